@@ -18,13 +18,13 @@
 // one call gives two doubles in (0, 1] of 53 bits each. Every link's numbers depend only on its
 // counter, so the result does not depend on the launch shape.
 //
-// The sweeps run on an even/odd structure-of-arrays copy of the links in the handle's workspace: plane
-// (mu, element, parity) holds that matrix element of U_mu at the sites of that parity, site s at
-// index s >> 1 (x is fastest and Nx is even, so s and s ^ 1 share an index and differ in parity).
-// A wave's 64 lanes take consecutive sites of one parity, so every load and store of a link element
-// is one contiguous 1 KB run. One thread per link; links of one direction and one parity share no
-// staple, so each (mu, parity) half is one launch. The canonical links ([site][mu][row][col]) are
-// packed before the first sweep of a call and unpacked after the last.
+// The sweeps run on an even/odd copy of the links in the handle's workspace: one array per parity, site s
+// at index s >> 1 (x is fastest and Nx is even, so s and s ^ 1 share an index and differ in parity), kept
+// in tiles of 64 indices with the 36 matrix elements of a tile one after another, 1 KB each. A wave's 64
+// lanes take consecutive sites of one parity, so every load and store of a link element is one run of
+// 1 KB (two at tile borders), and a tile's links lie in one 36 KB run. One thread per link; links of one
+// direction and one parity share no staple, so each (mu, parity) half is one launch. The canonical links
+// ([site][mu][row][col]) are packed before the first sweep of a call and unpacked after the last.
 #pragma once
 
 #include "gf_device.hpp"
@@ -33,7 +33,6 @@ namespace gf {
 
 constexpr int kMcThreads = 128;
 constexpr int kMcAttempts = 64;
-constexpr double kMcPi = 3.14159265358979323846;
 
 struct McGeom {
     int n[4];
@@ -41,36 +40,57 @@ struct McGeom {
     long long vol;
 };
 
-__device__ __forceinline__ void philox4x32_10(unsigned c[4], unsigned k0, unsigned k1) {
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        if (r > 0) {
-            k0 += 0x9E3779B9u;
-            k1 += 0xBB67AE85u;
-        }
-        const unsigned long long p0 = 0xD2511F53ull * (unsigned long long)c[0];
-        const unsigned long long p1 = 0xCD9E8D57ull * (unsigned long long)c[2];
-        const unsigned hi0 = (unsigned)(p0 >> 32), lo0 = (unsigned)p0;
-        const unsigned hi1 = (unsigned)(p1 >> 32), lo1 = (unsigned)p1;
-        const unsigned n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
-        c[0] = n0;
-        c[1] = lo1;
-        c[2] = n2;
-        c[3] = lo0;
-    }
-}
-
 struct McKey {
     unsigned k0, k1;
     unsigned word1;   // sweep or tag
     unsigned purpose;
 };
 
+// Philox4x32-10 on the counter (link, key.word1, word2, key.purpose). Only the link differs between the
+// lanes of a wave, so after two rounds half of the state still is the same for all of them: the products
+// with the link (round 1) and with what round 1 makes of it (round 2) are the same for every call on one
+// link and are formed once (McStream), and the other products of those rounds are scalar. 16 vector
+// products a call are left of 20, and they are most of a call's time.
+struct McStream {
+    unsigned lo1, hi2, lo2;  // low word of round 1's product with the link, both of round 2's
+};
+
+__device__ __forceinline__ McStream mc_stream(const McKey& key, unsigned link) {
+    const unsigned long long p = 0xD2511F53ull * (unsigned long long)link;
+    const unsigned c2 = (unsigned)(p >> 32) ^ key.purpose ^ key.k1;
+    const unsigned long long q = 0xCD9E8D57ull * (unsigned long long)c2;
+    return {(unsigned)p, (unsigned)(q >> 32), (unsigned)q};
+}
+
+__device__ __forceinline__ void philox4x32_10(const McKey& key, const McStream& st, unsigned word2, unsigned c[4]) {
+    // round 1: counter words 0, 1 become hi1 ^ word1 ^ k0 and lo1 of the product with word2
+    const unsigned long long p1 = 0xCD9E8D57ull * (unsigned long long)word2;
+    const unsigned a0 = (unsigned)(p1 >> 32) ^ key.word1 ^ key.k0, a1 = (unsigned)p1;
+    // round 2
+    unsigned k0 = key.k0 + 0x9E3779B9u, k1 = key.k1 + 0xBB67AE85u;
+    const unsigned long long p0 = 0xD2511F53ull * (unsigned long long)a0;
+    c[0] = st.hi2 ^ (a1 ^ k0);
+    c[1] = st.lo2;
+    c[2] = st.lo1 ^ ((unsigned)(p0 >> 32) ^ k1);
+    c[3] = (unsigned)p0;
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        const unsigned long long q0 = 0xD2511F53ull * (unsigned long long)c[0];
+        const unsigned long long q1 = 0xCD9E8D57ull * (unsigned long long)c[2];
+        c[0] = (unsigned)(q1 >> 32) ^ c[1] ^ k0;
+        c[1] = (unsigned)q1;
+        c[2] = (unsigned)(q0 >> 32) ^ c[3] ^ k1;
+        c[3] = (unsigned)q0;
+    }
+}
+
 // The two uniforms of Philox call `call` for this link, pair and hit.
-__device__ __forceinline__ void mc_uniforms(const McKey& key, unsigned link, int hit, int pair, int call, double& a,
+__device__ __forceinline__ void mc_uniforms(const McKey& key, const McStream& st, int hit, int pair, int call, double& a,
                                             double& b) {
-    unsigned c[4] = {link, key.word1, ((unsigned)hit << 20) | ((unsigned)pair << 16) | (unsigned)call, key.purpose};
-    philox4x32_10(c, key.k0, key.k1);
+    unsigned c[4];
+    philox4x32_10(key, st, ((unsigned)hit << 20) | ((unsigned)pair << 16) | (unsigned)call, c);
     const unsigned long long ma = ((unsigned long long)c[0] << 21) | (c[1] >> 11);
     const unsigned long long mb = ((unsigned long long)c[2] << 21) | (c[3] >> 11);
     const double scale = 1.1102230246251565e-16;  // 2^-53
@@ -89,35 +109,36 @@ __device__ __forceinline__ su3<double> mc_load(const double2* __restrict__ links
     return m;
 }
 
-__device__ __forceinline__ void mc_store(double2* __restrict__ links, long long s, int mu, const su3<double>& m) {
-    double2* p = links + (s * 4 + mu) * 9;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) p[k] = {m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im};
-}
-
-// Even/odd planes: P + ((mu*9 + e)*2 + parity) * hp + (s >> 1).
-struct McPlanes {
+// Even/odd tiles: element e of U_mu at site s, of parity par, is entry (mu*9 + e) of tile (s >> 1) / 64.
+constexpr int kMcTile = 64;
+constexpr int kMcEntries = 36;
+struct McTiles {
     double2* p;
-    size_t hp;  // elements per plane
+    size_t hp;  // elements per entry and parity (a multiple of the tile)
 };
 
 __device__ __forceinline__ int mc_parity(const int c[4]) { return (c[0] + c[1] + c[2] + c[3]) & 1; }
 
-__device__ __forceinline__ su3<double> eo_load(const McPlanes& P, long long s, int par, int mu) {
-    const double2* q = P.p + (size_t)(mu * 18 + par) * P.hp + (s >> 1);
+// The first entry of U_mu at index h of parity par; entry e is e * kMcTile further on.
+__device__ __forceinline__ double2* eo_at(const McTiles& P, unsigned h, int par, int mu) {
+    return P.p + (size_t)par * kMcEntries * P.hp + ((size_t)(h / kMcTile) * kMcEntries + mu * 9) * kMcTile + h % kMcTile;
+}
+
+__device__ __forceinline__ su3<double> eo_load(const McTiles& P, unsigned h, int par, int mu) {
+    const double2* q = eo_at(P, h, par, mu);
     su3<double> m;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const double2 v = q[(size_t)k * 2 * P.hp];
+        const double2 v = q[k * kMcTile];
         m.e[k / 3][k % 3] = {v.x, v.y};
     }
     return m;
 }
 
-__device__ __forceinline__ void eo_store(const McPlanes& P, long long s, int par, int mu, const su3<double>& m) {
-    double2* q = P.p + (size_t)(mu * 18 + par) * P.hp + (s >> 1);
+__device__ __forceinline__ void eo_store(const McTiles& P, unsigned h, int par, int mu, const su3<double>& m) {
+    double2* q = eo_at(P, h, par, mu);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) q[(size_t)k * 2 * P.hp] = {m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im};
+    for (int k = 0; k < 9; ++k) q[k * kMcTile] = {m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im};
 }
 
 // a * b^dagger
@@ -162,80 +183,85 @@ __device__ __forceinline__ long long mc_step(const McGeom& g, const int c[4], in
     return mc_site(g, e);
 }
 
-__device__ __forceinline__ long long mc_step2(const McGeom& g, const int c[4], int mu, int dm, int nu, int dn) {
-    int e[4] = {c[0], c[1], c[2], c[3]};
-    e[mu] += dm;
-    e[nu] += dn;
-    for (int d = 0; d < 4; ++d) {
-        if (e[d] < 0) e[d] += g.n[d];
-        if (e[d] >= g.n[d]) e[d] -= g.n[d];
+// A site and its neighbours one step up and down every axis, as site numbers (below 2^30: 2^32 links).
+struct McSite {
+    unsigned s, up[4], dn[4];
+};
+
+// Coordinates of site s.
+__device__ __forceinline__ void mc_coords(const McGeom& g, unsigned s, int c[4]) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const unsigned n = (unsigned)g.n[d], q = s / n;
+        c[d] = (int)(s - q * n);
+        s = q;
     }
-    return mc_site(g, e);
+    c[3] = (int)s;
 }
 
-// Staple sum of U_mu at site coordinates c.
-__device__ __forceinline__ su3<double> mc_staples(const double2* __restrict__ links, const McGeom& g, const int c[4],
-                                                  int mu) {
+// Block blk of a sweep over (x, y) planes of `plane` items, `threads` a block: the planes are visited with
+// z in groups of kMcZGroup inside the t loop, so that a plane's t neighbours were read kMcZGroup planes
+// earlier by the same XCD (whose blocks are consecutive, xcd_remap) and are still in its L2 (half-sweep at
+// 32^4: 223 us with blocks dealt round-robin, 193 in groups of 4, 197 and 194 in groups of 2 and 8). Every
+// link's update is independent of the order.
+constexpr unsigned kMcZGroup = 4;
+__device__ __forceinline__ unsigned mc_plane_order(const McGeom& g, unsigned blk, unsigned plane, unsigned threads) {
+    const unsigned nz = (unsigned)g.n[2], nt = (unsigned)g.n[3];
+    if (plane % threads != 0 || nz % kMcZGroup != 0 || nz <= kMcZGroup) return blk;
+    const unsigned bpp = plane / threads, pl = blk / bpp, off = blk - pl * bpp;
+    const unsigned z = pl % kMcZGroup + kMcZGroup * (pl / (kMcZGroup * nt)), t = (pl / kMcZGroup) % nt;
+    return (z + nz * t) * bpp + off;
+}
+
+__device__ __forceinline__ McSite mc_neighbours(const McGeom& g, const int c[4]) {
+    McSite m;
+    m.s = (unsigned)mc_site(g, c);
+    unsigned st = 1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const unsigned wrap = (unsigned)(g.n[d] - 1) * st;
+        m.up[d] = c[d] == g.n[d] - 1 ? m.s - wrap : m.s + st;
+        m.dn[d] = c[d] == 0 ? m.s + wrap : m.s - st;
+        st *= (unsigned)g.n[d];
+    }
+    return m;
+}
+
+__device__ __forceinline__ su3<double> mc_zero_matrix() {
     su3<double> a;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) a.e[i][j] = {0.0, 0.0};
-    const long long s = mc_site(g, c);
-    const long long s_pm = mc_step(g, c, mu, 1);
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        // U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-        {
-            const su3<double> t = mc_mul_adj(mc_load(links, s_pm, nu), mc_load(links, mc_step(g, c, nu, 1), mu));
-            const su3<double> up = mc_mul_adj(t, mc_load(links, s, nu));
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) a.e[i][j] = a.e[i][j] + up.e[i][j];
-        }
-        // U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu) = (U_mu(x-nu) U_nu(x+mu-nu))^dag U_nu(x-nu)
-        {
-            const long long s_mn = mc_step(g, c, nu, -1);
-            const su3<double> mb = mul(mc_load(links, s_mn, mu), mc_load(links, mc_step2(g, c, mu, 1, nu, -1), nu));
-            const su3<double> dn = mc_adj_mul(mb, mc_load(links, s_mn, nu));
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) a.e[i][j] = a.e[i][j] + dn.e[i][j];
-        }
-    }
     return a;
 }
 
-// Staple sum of U_mu at site coordinates c (parity p) from the even/odd planes; the same products in the
-// same order as mc_staples. Neighbours one step away have parity 1 - p, two steps away parity p.
-__device__ __forceinline__ su3<double> eo_staples(const McPlanes& P, const McGeom& g, const int c[4], int p, int mu) {
-    su3<double> a;
+__device__ __forceinline__ void mc_add(su3<double>& a, const su3<double>& b) {
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) a.e[i][j] = {0.0, 0.0};
-    const long long s = mc_site(g, c);
-    const long long s_pm = mc_step(g, c, mu, 1);
+        for (int j = 0; j < 3; ++j) a.e[i][j] = a.e[i][j] + b.e[i][j];
+}
+
+// Staple sum of U_MU at a site of parity p from the even/odd tiles: for every other axis nu the upper staple,
+// then the lower. Neighbours one step away have parity 1 - p, two steps away (x + mu - nu, the two steps are
+// independent) parity p. MU is a template parameter so that the three planes unroll and the loads of one run
+// ahead of the products of another.
+template <int MU>
+__device__ __forceinline__ su3<double> eo_staples(const McTiles& P, const McSite& m, int p) {
+    su3<double> a = mc_zero_matrix();
+#pragma unroll
     for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
+        if (nu == MU) continue;
+        const unsigned s_pm = m.up[MU], s_mn = m.dn[nu];
         {
-            const su3<double> t = mc_mul_adj(eo_load(P, s_pm, 1 - p, nu), eo_load(P, mc_step(g, c, nu, 1), 1 - p, mu));
-            const su3<double> up = mc_mul_adj(t, eo_load(P, s, p, nu));
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) a.e[i][j] = a.e[i][j] + up.e[i][j];
+            const su3<double> t = mc_mul_adj(eo_load(P, s_pm >> 1, 1 - p, nu), eo_load(P, m.up[nu] >> 1, 1 - p, MU));
+            mc_add(a, mc_mul_adj(t, eo_load(P, m.s >> 1, p, nu)));
         }
         {
-            const long long s_mn = mc_step(g, c, nu, -1);
-            const su3<double> mb = mul(eo_load(P, s_mn, 1 - p, mu), eo_load(P, mc_step2(g, c, mu, 1, nu, -1), p, nu));
-            const su3<double> dn = mc_adj_mul(mb, eo_load(P, s_mn, 1 - p, nu));
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) a.e[i][j] = a.e[i][j] + dn.e[i][j];
+            const su3<double> mb =
+                mul(eo_load(P, s_mn >> 1, 1 - p, MU), eo_load(P, (s_pm + (s_mn - m.s)) >> 1, p, nu));
+            mc_add(a, mc_adj_mul(mb, eo_load(P, s_mn >> 1, 1 - p, nu)));
         }
     }
     return a;
@@ -267,7 +293,7 @@ __device__ __forceinline__ void su2_embed_left(const Su2& s, su3<double>& m, int
 // because every Kennedy-Pendleton attempt was rejected.
 template <bool OR>
 __device__ __forceinline__ int mc_cm_update(su3<double>& u, const su3<double>& a, double beta, const McKey& key,
-                                            unsigned link, int hit) {
+                                            const McStream& st, int hit) {
     su3<double> w = mul(u, a);
     int rejected = 0;
 #pragma unroll
@@ -283,14 +309,16 @@ __device__ __forceinline__ int mc_cm_update(su3<double>& u, const su3<double>& a
         if (OR) {
             s = su2_mul(v, v);
         } else {
+            // the angles are 2 pi times a uniform: cospi and sincospi reduce them exactly, without the general
+            // reduction of a radian argument (with the second wave per SIMD, 118 -> 90 us a hit at 32^4)
             const double alpha = 2.0 * beta * k / 3.0;
             double x0 = 1.0;
             bool ok = false;
             for (int t = 1; t <= kMcAttempts && !ok; ++t) {
                 double u1, u2, u3, u4;
-                mc_uniforms(key, link, hit, p, 2 * t - 1, u1, u2);
-                mc_uniforms(key, link, hit, p, 2 * t, u3, u4);
-                const double cs = cos(2.0 * kMcPi * u2);
+                mc_uniforms(key, st, hit, p, 2 * t - 1, u1, u2);
+                mc_uniforms(key, st, hit, p, 2 * t, u3, u4);
+                const double cs = cospi(2.0 * u2);
                 const double delta = -(log(u1) + cs * cs * log(u3)) / alpha;
                 if (u4 * u4 <= 1.0 - 0.5 * delta) {
                     x0 = 1.0 - delta;
@@ -302,12 +330,13 @@ __device__ __forceinline__ int mc_cm_update(su3<double>& u, const su3<double>& a
                 continue;
             }
             double cu, pu;
-            mc_uniforms(key, link, hit, p, 0, cu, pu);
+            mc_uniforms(key, st, hit, p, 0, cu, pu);
             const double cos_t = 2.0 * cu - 1.0;
             const double sin_t = sqrt(fmax(0.0, 1.0 - cos_t * cos_t));
-            const double phi = 2.0 * kMcPi * pu;
+            double sin_p, cos_p;
+            sincospi(2.0 * pu, &sin_p, &cos_p);
             const double rad = sqrt(fmax(0.0, 1.0 - x0 * x0));
-            s = su2_mul(su2_quat(x0, rad * sin_t * cos(phi), rad * sin_t * sin(phi), rad * cos_t), v);
+            s = su2_mul(su2_quat(x0, rad * sin_t * cos_p, rad * sin_t * sin_p, rad * cos_t), v);
         }
         su2_embed_left(s, u, i, j);
         su2_embed_left(s, w, i, j);
@@ -315,41 +344,32 @@ __device__ __forceinline__ int mc_cm_update(su3<double>& u, const su3<double>& a
     return rejected;
 }
 
-// One (mu, parity) half-sweep: thread h updates the h-th link of direction mu among the sites of the
+// One (MU, parity) half-sweep: thread h updates the h-th link of direction MU among the sites of the
 // given parity, in lexicographic order. Block b adds its count of rejected pair updates to rej[b]
 // (plain stores: the launches of a sweep are ordered on one stream).
-template <bool OR>
-__global__ void __launch_bounds__(kMcThreads) k_mc_update(McPlanes P, McGeom g, int mu, int parity, double beta,
-                                                          McKey key, unsigned* __restrict__ rej) {
+//
+// Bound by memory: a lane reads 19 matrices (2.7 KB), which the L1s do not hold between lanes, so every one
+// is an L2 read, and the field itself (576 B per site) comes through the L2s once if the blocks in flight
+// stay close together. The launch therefore asks for LDS it does not use, which holds a CU to few blocks:
+// over-relaxation two (four waves; 32^4: 193 -> 156 us a half-sweep, 158 with three KB less, 165 with one
+// block), heatbath three (its arithmetic wants more waves: 183 -> 178 us, 198 with two).
+constexpr size_t kMcLdsHeatbath = 50000, kMcLdsOverrelax = 64000;
+template <int MU, bool OR>
+__global__ void __launch_bounds__(kMcThreads) k_mc_update(McTiles P, McGeom g, int parity, double beta, McKey key,
+                                                          unsigned* __restrict__ rej) {
     __shared__ unsigned red[kMcThreads];
-    // Blocks visit the (x, y) planes with z in pairs inside the t loop, (z mod 2, t, z / 2), so that the t
-    // neighbours were read two planes earlier and are still in the XCD's L2 (3.8 % faster per sweep at
-    // 32^4 than the plain lexicographic order; groups of 4 and 8 were no better). Each link's update
-    // does not depend on the order.
-    long long h = (long long)blockIdx.x * kMcThreads + threadIdx.x;
-    {
-        const long long hpp = (long long)g.half_x * g.n[1];  // half-sites per (x, y) plane
-        if (hpp % kMcThreads == 0 && g.n[2] % 2 == 0 && g.n[2] > 2) {
-            const long long bpp = hpp / kMcThreads;
-            const long long b = blockIdx.x, P = b / bpp, off = b - P * bpp;
-            const long long z = P % 2 + 2 * (P / (2 * g.n[3]));
-            const long long t = (P / 2) % g.n[3];
-            h = ((z + (long long)g.n[2] * t) * bpp + off) * kMcThreads + threadIdx.x;
-        }
-    }
+    const unsigned h = mc_plane_order(g, (unsigned)xcd_remap(blockIdx.x, gridDim.x),
+                                      (unsigned)(g.half_x * g.n[1]), kMcThreads) * kMcThreads + threadIdx.x;
     unsigned rj = 0;
-    if (h < g.vol / 2) {
-        const long long row = h / g.half_x;
+    if (h < (unsigned)(g.vol / 2)) {
         int c[4];
-        c[1] = (int)(row % g.n[1]);
-        c[2] = (int)((row / g.n[1]) % g.n[2]);
-        c[3] = (int)(row / ((long long)g.n[1] * g.n[2]));
-        c[0] = 2 * (int)(h - row * g.half_x) + ((c[1] + c[2] + c[3] + parity) & 1);
-        const long long s = mc_site(g, c);
-        const su3<double> a = eo_staples(P, g, c, parity, mu);
-        su3<double> u = eo_load(P, s, parity, mu);
-        rj = (unsigned)mc_cm_update<OR>(u, a, beta, key, (unsigned)(s * 4 + mu), 0);
-        eo_store(P, s, parity, mu, u);
+        mc_coords(g, 2 * h, c);
+        c[0] += mc_parity(c) != parity;
+        const McSite m = mc_neighbours(g, c);
+        const su3<double> a = eo_staples<MU>(P, m, parity);
+        su3<double> u = eo_load(P, m.s >> 1, parity, MU);
+        rj = (unsigned)mc_cm_update<OR>(u, a, beta, key, OR ? McStream{} : mc_stream(key, m.s * 4 + MU), 0);
+        eo_store(P, m.s >> 1, parity, MU, u);
     }
     if (OR) return;
     red[threadIdx.x] = rj;
@@ -361,49 +381,63 @@ __global__ void __launch_bounds__(kMcThreads) k_mc_update(McPlanes P, McGeom g, 
     if (threadIdx.x == 0 && red[0]) rej[blockIdx.x] += red[0];
 }
 
-// Canonical links <-> even/odd planes, one thread per site.
-__global__ void __launch_bounds__(256) k_mc_pack(const double2* __restrict__ links, McPlanes P, McGeom g) {
-    const long long s = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (s >= g.vol) return;
+// Canonical links <-> even/odd tiles. A block moves kMcIoSites consecutive sites (kMcIoSites / 2 indices of
+// either parity) through LDS, so that the canonical side is one contiguous run and the tile side runs of
+// kMcIoSites / 2 elements (32^4: one thread per site took 282 us in and 407 out; 200 and 240 this way, the
+// last with the reunitarisation, a pass of 182 us before). A site's row in LDS is 37 elements (36 + 1).
+constexpr int kMcIoSites = 64;
+constexpr int kMcIoRow = kMcEntries + 1;
+
+// Parity of site s.
+__device__ __forceinline__ int mc_site_parity(const McGeom& g, unsigned s) {
     int c[4];
-    long long r = s;
-    for (int d = 0; d < 4; ++d) {
-        c[d] = (int)(r % g.n[d]);
-        r /= g.n[d];
-    }
-    const int par = mc_parity(c);
-    for (int mu = 0; mu < 4; ++mu) eo_store(P, s, par, mu, mc_load(links, s, mu));
+    mc_coords(g, s, c);
+    return mc_parity(c);
 }
 
-__global__ void __launch_bounds__(256) k_mc_unpack(McPlanes P, McGeom g, double2* __restrict__ links) {
-    const long long s = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (s >= g.vol) return;
-    int c[4];
-    long long r = s;
-    for (int d = 0; d < 4; ++d) {
-        c[d] = (int)(r % g.n[d]);
-        r /= g.n[d];
+__global__ void __launch_bounds__(256) k_mc_pack(const double2* __restrict__ links, McTiles P, McGeom g) {
+    __shared__ double2 row[kMcIoSites * kMcIoRow];
+    const unsigned s0 = blockIdx.x * kMcIoSites;
+    const unsigned left = (unsigned)g.vol - s0, ns = left < kMcIoSites ? left : kMcIoSites;
+    const double2* src = links + (size_t)s0 * kMcEntries;
+    for (unsigned i = threadIdx.x; i < ns * kMcEntries; i += 256) row[(i / kMcEntries) * kMcIoRow + i % kMcEntries] = src[i];
+    __syncthreads();
+    // lane q of a wave: parity q / 32, index q % 32; the waves share the 36 entries
+    const unsigned q = threadIdx.x & 63, w = threadIdx.x >> 6, i = q & 31;
+    if (2 * i < ns) {
+        const int par = (int)(q >> 5), odd = mc_site_parity(g, s0 + 2 * i) != par;  // which of the two sites has it
+        double2* dst = eo_at(P, (s0 >> 1) + i, par, 0);
+        for (unsigned k = w * 9; k < w * 9 + 9; ++k) dst[k * kMcTile] = row[(2 * i + odd) * kMcIoRow + k];
     }
-    const int par = mc_parity(c);
-    for (int mu = 0; mu < 4; ++mu) mc_store(links, s, mu, eo_load(P, s, par, mu));
 }
 
-// Every link reunitarised in the planes: thread per (site of one parity index, parity, mu).
-__global__ void __launch_bounds__(256) k_mc_reunit(McPlanes P, long long half) {
-    const long long l = (long long)blockIdx.x * 256 + threadIdx.x;  // l = (mu * 2 + parity) * half + h
-    if (l >= 8 * half) return;
-    const long long h = l % half;
-    const int mp = (int)(l / half), mu = mp >> 1, par = mp & 1;
-    double2* q = P.p + (size_t)(mu * 18 + par) * P.hp + h;
-    su3<double> m;
+// reunit: every link is reunitarised on its way out (the end of a sweep).
+__global__ void __launch_bounds__(256) k_mc_unpack(McTiles P, McGeom g, double2* __restrict__ links, int reunit) {
+    __shared__ double2 row[kMcIoSites * kMcIoRow];
+    const unsigned s0 = blockIdx.x * kMcIoSites;
+    const unsigned left = (unsigned)g.vol - s0, ns = left < kMcIoSites ? left : kMcIoSites;
+    const unsigned q = threadIdx.x & 63, mu = threadIdx.x >> 6, i = q & 31;
+    if (2 * i < ns) {
+        const int par = (int)(q >> 5), odd = mc_site_parity(g, s0 + 2 * i) != par;
+        su3<double> m = eo_load(P, (s0 >> 1) + i, par, (int)mu);
+        if (reunit) reunitarize(m);
+        double2* dst = row + (2 * i + odd) * kMcIoRow + mu * 9;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const double2 v = q[(size_t)k * 2 * P.hp];
-        m.e[k / 3][k % 3] = {v.x, v.y};
+        for (int k = 0; k < 9; ++k) dst[k] = {m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im};
     }
+    __syncthreads();
+    double2* dst = links + (size_t)s0 * kMcEntries;
+    for (unsigned j = threadIdx.x; j < ns * kMcEntries; j += 256) dst[j] = row[(j / kMcEntries) * kMcIoRow + j % kMcEntries];
+}
+
+// Every link reunitarised in the tiles (between the sweeps of one call): thread per (mu, parity, index).
+__global__ void __launch_bounds__(256) k_mc_reunit(McTiles P, unsigned half) {
+    const unsigned h = blockIdx.x * 256 + threadIdx.x;
+    if (h >= half) return;
+    const int mu = (int)blockIdx.y >> 1, par = (int)blockIdx.y & 1;
+    su3<double> m = eo_load(P, h, par, mu);
     reunitarize(m);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) q[(size_t)k * 2 * P.hp] = {m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im};
+    eo_store(P, h, par, mu, m);
 }
 
 __global__ void __launch_bounds__(256) k_mc_zero(unsigned* __restrict__ p, int n) {
@@ -426,33 +460,42 @@ __global__ void __launch_bounds__(256) k_mc_count(const unsigned* __restrict__ p
     if (threadIdx.x == 0) *out = red[0];
 }
 
-// Multi-hit average of every temporal link, out as complex double [site][row][col].
-__global__ void __launch_bounds__(kMcThreads) k_mc_multihit(const double2* __restrict__ links, McGeom g,
-                                                            double beta, McKey key, int nhits,
-                                                            double2* __restrict__ out) {
-    const long long s = (long long)blockIdx.x * kMcThreads + threadIdx.x;
-    if (s >= g.vol) return;
-    int c[4];
-    long long r = s;
-    for (int d = 0; d < 4; ++d) {
-        c[d] = (int)(r % g.n[d]);
-        r /= g.n[d];
+// Multi-hit average of every temporal link, out as complex double [site][row][col], straight from the
+// canonical links. The staples are bound by memory (a lane's 144-byte links lie in two 128-byte lines, 5 KB
+// of lines per site) and the hits by arithmetic: with two waves per SIMD one covers the other. Measured at
+// 32^4 with 8 hits: 1385 us at one wave per SIMD (260 registers), 895 at two; the staple sums in a kernel
+// of their own 1150, packing into the tiles first 1040. One-wave blocks: they spread evenly over the SIMDs
+// of a small lattice (16^4: 125 us with two-wave blocks, 88).
+constexpr int kMhThreads = 64;
+__global__ void __launch_bounds__(kMhThreads, 2) k_mc_multihit(const double2* __restrict__ links, McGeom g, double beta,
+                                                               McKey key, int nhits, double2* __restrict__ out) {
+    const unsigned s = mc_plane_order(g, (unsigned)xcd_remap(blockIdx.x, gridDim.x), (unsigned)(g.n[0] * g.n[1]),
+                                      kMhThreads) * kMhThreads + threadIdx.x;
+    if (s >= (unsigned)g.vol) return;
+    su3<double> a = mc_zero_matrix();
+    {
+        int c[4];
+        mc_coords(g, s, c);
+        const McSite m = mc_neighbours(g, c);
+        const unsigned s_pt = m.up[3];
+#pragma unroll 1
+        for (int nu = 0; nu < 3; ++nu) {  // not unrolled: the loads of three planes in flight take the registers
+            const unsigned s_pn = nu == 0 ? m.up[0] : nu == 1 ? m.up[1] : m.up[2];
+            const unsigned s_mn = nu == 0 ? m.dn[0] : nu == 1 ? m.dn[1] : m.dn[2];
+            const su3<double> t = mc_mul_adj(mc_load(links, s_pt, nu), mc_load(links, s_pn, 3));
+            mc_add(a, mc_mul_adj(t, mc_load(links, s, nu)));
+            const su3<double> mb = mul(mc_load(links, s_mn, 3), mc_load(links, s_pt + (s_mn - s), nu));
+            mc_add(a, mc_adj_mul(mb, mc_load(links, s_mn, nu)));
+        }
     }
-    const su3<double> a = mc_staples(links, g, c, 3);
     su3<double> u = mc_load(links, s, 3);
-    su3<double> acc;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) acc.e[i][j] = {0.0, 0.0};
+    su3<double> acc = mc_zero_matrix();
+    const McStream st = mc_stream(key, s * 4 + 3);
     for (int h = 0; h < nhits; ++h) {
-        (void)mc_cm_update<false>(u, a, beta, key, (unsigned)(s * 4 + 3), h);
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) acc.e[i][j] = acc.e[i][j] + u.e[i][j];
+        (void)mc_cm_update<false>(u, a, beta, key, st, h);
+        mc_add(acc, u);
     }
-    double2* p = out + s * 9;
+    double2* p = out + (size_t)s * 9;
 #pragma unroll
     for (int k = 0; k < 9; ++k) p[k] = {acc.e[k / 3][k % 3].re / nhits, acc.e[k / 3][k % 3].im / nhits};
 }

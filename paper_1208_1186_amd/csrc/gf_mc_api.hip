@@ -1,12 +1,12 @@
 // libgf host side of the Monte Carlo input generator (gf_mc_* in include/gf.h).
 //
 // The handle keeps the lattice shape, beta, the seed and a workspace of the
-// caller's: the even/odd link planes the sweeps run on (72 planes of V/2
-// complex doubles), per-block counters of rejected heatbath pair updates,
+// caller's: the even/odd link tiles the sweeps run on (36 entries of V/2
+// complex doubles per parity), per-block counters of rejected heatbath pair updates,
 // plaquette partials and two result scalars. A call packs the canonical links
-// into the planes, runs its sweeps (8 launches per heatbath or over-relaxation
-// pass: 4 directions x 2 parities; then one reunitarisation launch) and
-// unpacks; all on the handle's stream.
+// into the tiles, runs its sweeps (8 launches per heatbath or over-relaxation
+// pass: 4 directions x 2 parities; one reunitarisation launch between
+// sweeps) and unpacks, reunitarising the last sweep's links on their way out; all on the handle's stream.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -20,7 +20,7 @@ using namespace gf;
 
 struct gf_mc {
     McGeom g;
-    McPlanes P;
+    McTiles P;
     double beta;
     unsigned long long seed;
     int nblk_half;  // blocks of one (mu, parity) launch
@@ -46,7 +46,7 @@ struct McLayout {
     McGeom g;
     int nblk_half, nblk_plaq;
     size_t hp;
-    size_t off_planes, off_rej, off_part, off_count, off_plaq, total;
+    size_t off_tiles, off_rej, off_part, off_count, off_plaq, total;
 };
 
 gf_status mc_layout(const int32_t* dims, McLayout& L, std::string& err) {
@@ -78,7 +78,7 @@ gf_status mc_layout(const int32_t* dims, McLayout& L, std::string& err) {
     L.nblk_plaq = (int)((vol + 255) / 256);
     L.hp = (size_t)(vol / 2 + 255) / 256 * 256;
     size_t o = 0;
-    L.off_planes = o;
+    L.off_tiles = o;
     o = mc_align(o + 72 * L.hp * sizeof(double2));
     L.off_rej = o;
     o = mc_align(o + (size_t)L.nblk_half * sizeof(unsigned));
@@ -101,6 +101,20 @@ gf_status mcheck(gf_mc* m, hipError_t e, const char* what) {
     if (e == hipSuccess) return GF_OK;
     return mfail(m, GF_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
+
+unsigned io_blocks(const gf_mc* m) { return (unsigned)((m->g.vol + kMcIoSites - 1) / kMcIoSites); }
+
+// Canonical links into the handle's even/odd tiles.
+gf_status pack(gf_mc* m, const double2* links) {
+    hipLaunchKernelGGL(k_mc_pack, dim3(io_blocks(m)), dim3(256), 0, m->st, links, m->P, m->g);
+    return mcheck(m, hipGetLastError(), "pack launch");
+}
+
+// The half-sweep kernels: [over-relaxation][direction].
+using McUpdate = void (*)(McTiles, McGeom, int, double, McKey, unsigned*);
+const McUpdate kUpdate[2][4] = {
+    {k_mc_update<0, false>, k_mc_update<1, false>, k_mc_update<2, false>, k_mc_update<3, false>},
+    {k_mc_update<0, true>, k_mc_update<1, true>, k_mc_update<2, true>, k_mc_update<3, true>}};
 
 McKey make_key(const gf_mc* m, unsigned word1, unsigned purpose) {
     return {(unsigned)(m->seed & 0xFFFFFFFFull), (unsigned)(m->seed >> 32), word1, purpose};
@@ -149,7 +163,7 @@ gf_status gf_mc_create(gf_mc** out, const int32_t* dims, double beta, uint64_t s
     m->nblk_half = L.nblk_half;
     m->nblk_plaq = L.nblk_plaq;
     unsigned char* ws = static_cast<unsigned char*>(d_workspace);
-    m->P = {reinterpret_cast<double2*>(ws + L.off_planes), L.hp};
+    m->P = {reinterpret_cast<double2*>(ws + L.off_tiles), L.hp};
     m->rej = reinterpret_cast<unsigned*>(ws + L.off_rej);
     m->part = reinterpret_cast<double*>(ws + L.off_part);
     m->d_count = reinterpret_cast<unsigned long long*>(ws + L.off_count);
@@ -167,32 +181,25 @@ gf_status gf_mc_update(gf_mc* m, double* d_links, uint64_t first_sweep, int32_t 
     if (first_sweep + (uint64_t)n_sweeps - 1 > 0xFFFFFFFFull) return mfail(m, GF_EINVAL, "sweeps must fit in 32 bits");
     if (n_overrelax < 0 || n_overrelax > 64) return mfail(m, GF_EINVAL, "n_overrelax must be in [0, 64]");
     double2* links = reinterpret_cast<double2*>(d_links);
-    const unsigned nsite_blk = (unsigned)((m->g.vol + 255) / 256);
     hipLaunchKernelGGL(k_mc_zero, dim3((m->nblk_half + 255) / 256), dim3(256), 0, m->st, m->rej, m->nblk_half);
     gf_status s = mcheck(m, hipGetLastError(), "counter reset launch");
     if (s != GF_OK) return s;
-    hipLaunchKernelGGL(k_mc_pack, dim3(nsite_blk), dim3(256), 0, m->st, links, m->P, m->g);
-    if ((s = mcheck(m, hipGetLastError(), "pack launch")) != GF_OK) return s;
-    const long long half = m->g.vol / 2;
-    for (int32_t k = 0; k < n_sweeps && s == GF_OK; ++k) {
+    if ((s = pack(m, links)) != GF_OK) return s;
+    const unsigned half = (unsigned)(m->g.vol / 2);
+    for (int32_t k = 0; k < n_sweeps; ++k) {
         const McKey key = make_key(m, (unsigned)(first_sweep + k), 0);
-        for (int rep = 0; rep <= n_overrelax && s == GF_OK; ++rep)
-            for (int mu = 0; mu < 4 && s == GF_OK; ++mu)
-                for (int par = 0; par < 2 && s == GF_OK; ++par) {
-                    if (rep == 0)
-                        hipLaunchKernelGGL(k_mc_update<false>, dim3(m->nblk_half), dim3(kMcThreads), 0, m->st, m->P,
-                                           m->g, mu, par, m->beta, key, m->rej);
-                    else
-                        hipLaunchKernelGGL(k_mc_update<true>, dim3(m->nblk_half), dim3(kMcThreads), 0, m->st, m->P,
-                                           m->g, mu, par, m->beta, key, m->rej);
-                    s = mcheck(m, hipGetLastError(), "update launch");
+        for (int rep = 0; rep <= n_overrelax; ++rep)
+            for (int mu = 0; mu < 4; ++mu)
+                for (int par = 0; par < 2; ++par) {
+                    hipLaunchKernelGGL(kUpdate[rep == 0 ? 0 : 1][mu], dim3(m->nblk_half), dim3(kMcThreads), rep == 0 ? kMcLdsHeatbath : kMcLdsOverrelax, m->st,
+                                       m->P, m->g, par, m->beta, key, m->rej);
+                    if ((s = mcheck(m, hipGetLastError(), "update launch")) != GF_OK) return s;
                 }
-        if (s != GF_OK) return s;
-        hipLaunchKernelGGL(k_mc_reunit, dim3((unsigned)((8 * half + 255) / 256)), dim3(256), 0, m->st, m->P, half);
-        s = mcheck(m, hipGetLastError(), "reunitarisation launch");
+        if (k + 1 == n_sweeps) break;  // the last sweep's reunitarisation is part of the unpacking
+        hipLaunchKernelGGL(k_mc_reunit, dim3((half + 255) / 256, 8), dim3(256), 0, m->st, m->P, half);
+        if ((s = mcheck(m, hipGetLastError(), "reunitarisation launch")) != GF_OK) return s;
     }
-    if (s != GF_OK) return s;
-    hipLaunchKernelGGL(k_mc_unpack, dim3(nsite_blk), dim3(256), 0, m->st, m->P, m->g, links);
+    hipLaunchKernelGGL(k_mc_unpack, dim3(io_blocks(m)), dim3(256), 0, m->st, m->P, m->g, links, 1);
     if ((s = mcheck(m, hipGetLastError(), "unpack launch")) != GF_OK) return s;
     if (h_rejected) {
         hipLaunchKernelGGL(k_mc_count, dim3(1), dim3(256), 0, m->st, m->rej, m->nblk_half, m->d_count);
@@ -212,7 +219,10 @@ gf_status gf_mc_multihit(gf_mc* m, const double* d_links, uint64_t tag, int32_t 
     if (!d_links || !d_out) return mfail(m, GF_EINVAL, "d_links or d_out is NULL");
     if (tag > 0xFFFFFFFFull) return mfail(m, GF_EINVAL, "tag must fit in 32 bits");
     if (n_hits < 1 || n_hits > 4095) return mfail(m, GF_EINVAL, "n_hits must be in [1, 4095]");
-    hipLaunchKernelGGL(k_mc_multihit, dim3((unsigned)((m->g.vol + kMcThreads - 1) / kMcThreads)), dim3(kMcThreads), 0,
+    // a single hit does not cover the staples: hold a CU to one wave per SIMD by LDS that is not used, which
+    // keeps the L1s from turning over (32^4: 586 -> 556 us; from two hits on the second wave is faster)
+    const size_t lds = n_hits == 1 ? 40000 : 0;
+    hipLaunchKernelGGL(k_mc_multihit, dim3((unsigned)((m->g.vol + kMhThreads - 1) / kMhThreads)), dim3(kMhThreads), lds,
                        m->st, reinterpret_cast<const double2*>(d_links), m->g, m->beta, make_key(m, (unsigned)tag, 1),
                        n_hits, reinterpret_cast<double2*>(d_out));
     return mcheck(m, hipGetLastError(), "multi-hit launch");

@@ -67,6 +67,26 @@ def test_multihit_matches_oracle(dims, beta, n_hits):
     m.close()
 
 
+@pytest.mark.parametrize("dims,n_or,n_hits", [
+    ((2, 2, 2, 2), 1, 1),    # 8 sites of a parity in a tile of 64; neighbours up and down are the same site
+    ((6, 10, 2, 4), 2, 2),   # 240: the last tile and the last 64-site run are part full
+    ((32, 8, 8, 2), 1, 1),   # whole tiles, planes visited with z in groups; one hit (its own launch)
+    ((16, 8, 8, 2), 1, 12),  # z in groups for the multi-hit only
+])
+def test_tiles_and_orders_match_oracle(dims, n_or, n_hits):
+    """Where the even/odd tiles, the runs of 64 sites and the plane orders have their edges; the bound of the
+    tests above (ulp-level differences of log, cos and sqrt)."""
+    u = synth.make_config(dims, 13)
+    links = torch.from_numpy(u).cuda()
+    m = gf.MonteCarlo(dims, 6.0, 1 << 40)
+    rej = m.update(links, 3, n_or, count_rejected=True)
+    want, wrej = mc.update(u, 6.0, 1 << 40, 3, n_or)
+    assert rej == wrej and np.max(np.abs(links.cpu().numpy() - want)) < 1e-12
+    got = m.multihit(links, 7, n_hits).cpu().numpy()
+    assert np.max(np.abs(got - mc.multihit(links.cpu().numpy(), 6.0, 1 << 40, 7, n_hits))) < 1e-12
+    m.close()
+
+
 def test_overrelaxation_and_unitarity_at_32x32x32x32():
     dims = (32, 32, 32, 32)
     links = torch.from_numpy(synth.make_config(dims, 0)).cuda()
