@@ -918,30 +918,47 @@ std::vector<int> zt_candidates(const Layout& L) {
 constexpr int kTuneReps = 10;
 constexpr int kTuneRounds = 3;
 
+// Keeps the stream busy while the host queues the trial launches behind it, so that short kernels are timed
+// back to back: launched one by one they take as long as the host needs per launch (about 5 us), whichever
+// tiling they are, and the choice was noise (16^4 in double kept 16 or 8 (z, t) columns, 9.3 and 8.3 us a
+// launch, over 4 columns, 6.9). Ends by the clock, and by its count if the clock stood still.
+__global__ void k_tune_delay(long long ticks) {
+    const long long t0 = wall_clock64();
+    for (int i = 0; i < (1 << 16) && wall_clock64() - t0 < ticks; ++i) __builtin_amdgcn_s_sleep(1);
+}
+constexpr long long kTuneDelayTicks = 10000;  // of the 100 MHz counter: 100 us
+
+// Milliseconds of kTuneReps trial launches queued by run(), back to back, after two to warm up.
+template <typename F>
+double time_launches(gf_ctx* c, F run) {
+    hipEvent_t a = nullptr, b = nullptr;
+    double out = 1e30;
+    if (hipEventCreateWithFlags(&a, hipEventDisableSystemFence) == hipSuccess &&
+        hipEventCreateWithFlags(&b, hipEventDisableSystemFence) == hipSuccess) {
+        run();
+        run();
+        hipLaunchKernelGGL(k_tune_delay, dim3(1), dim3(64), 0, c->st, kTuneDelayTicks);
+        (void)hipEventRecord(a, c->st);
+        for (int i = 0; i < kTuneReps; ++i) run();
+        (void)hipEventRecord(b, c->st);
+        float ms = 1e30f;
+        if (hipGetLastError() == hipSuccess && hipEventSynchronize(b) == hipSuccess &&
+            hipEventElapsedTime(&ms, a, b) == hipSuccess)
+            out = ms;
+    }
+    if (a) (void)hipEventDestroy(a);
+    if (b) (void)hipEventDestroy(b);
+    return out;
+}
+
 template <typename T>
 double time_pass(gf_ctx* c, bool xy) {
-    hipEvent_t a = nullptr, b = nullptr;
-    if (hipEventCreateWithFlags(&a, hipEventDisableSystemFence) != hipSuccess ||
-        hipEventCreateWithFlags(&b, hipEventDisableSystemFence) != hipSuccess)
-        return 1e30;
-    auto run = [&]() {
+    return time_launches(c, [&]() {
         if (xy)
             launch_xy<T, false>(c, c->D, c->Q, 1, false);
         else
             launch_zt<T>(c, c->Q, 1);
-    };
-    run();
-    run();
-    (void)hipEventRecord(a, c->st);
-    for (int i = 0; i < kTuneReps; ++i) run();
-    (void)hipEventRecord(b, c->st);
-    float ms = 1e30f;
-    if (hipGetLastError() != hipSuccess || hipEventSynchronize(b) != hipSuccess ||
-        hipEventElapsedTime(&ms, a, b) != hipSuccess)
-        ms = 1e30f;
-    (void)hipEventDestroy(a);
-    (void)hipEventDestroy(b);
-    return ms;
+    });
 }
 
 // Traversals the loop kernel can take on this shape: z groupings (1 always), 0 (blocks step through t)
@@ -961,23 +978,7 @@ std::vector<int> zb_candidates(const Layout& L) {
 template <typename T, int NE>
 void time_loop_t(gf_ctx* c, double& ms_out) {
     // trial launches on the current links: divergence -> Q, partials of a scratch control-block head
-    auto run = [&]() { launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->Q, 1); };
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    ms_out = 1e30;
-    if (hipEventCreateWithFlags(&e0, hipEventDisableSystemFence) != hipSuccess ||
-        hipEventCreateWithFlags(&e1, hipEventDisableSystemFence) != hipSuccess)
-        return;
-    run();
-    run();
-    (void)hipEventRecord(e0, c->st);
-    for (int i = 0; i < kTuneReps; ++i) run();
-    (void)hipEventRecord(e1, c->st);
-    float ms = 1e30f;
-    if (hipGetLastError() == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
-        hipEventElapsedTime(&ms, e0, e1) == hipSuccess)
-        ms_out = ms;
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
+    ms_out = time_launches(c, [&]() { launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->Q, 1); });
 }
 
 gf_status autotune(gf_ctx* c) {
@@ -2744,13 +2745,13 @@ gf_status gf_record_spectra(gf_ctx* c, int64_t n, double probe_scale, double* d_
         if (s == GF_OK && i >= 1) {
             const int a = (i - 1) & 1, b = i & 1, pb = 2 + ((i - 1) & 1);
             if (c->L.fp32)
-                hipLaunchKernelGGL(k_record_tuples<float>, dim3((c->L.ntuples + 255) / 256), dim3(256), 0, c->st,
+                hipLaunchKernelGGL(k_record_tuples<float>, dim3((c->L.ntuples + kRecordTuples - 1) / kRecordTuples), dim3(256), 0, c->st,
                                    reinterpret_cast<const cx<float>*>(c->spec[a]),
                                    reinterpret_cast<const cx<float>*>(c->spec[b]),
                                    reinterpret_cast<const cx<float>*>(c->spec[pb]), c->L.ps, c->tg,
                                    d_records + (size_t)(i - 1) * recn);
             else
-                hipLaunchKernelGGL(k_record_tuples<double>, dim3((c->L.ntuples + 255) / 256), dim3(256), 0, c->st,
+                hipLaunchKernelGGL(k_record_tuples<double>, dim3((c->L.ntuples + kRecordTuples - 1) / kRecordTuples), dim3(256), 0, c->st,
                                    reinterpret_cast<const cx<double>*>(c->spec[a]),
                                    reinterpret_cast<const cx<double>*>(c->spec[b]),
                                    reinterpret_cast<const cx<double>*>(c->spec[pb]), c->L.ps, c->tg,
