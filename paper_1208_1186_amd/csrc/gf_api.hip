@@ -2775,10 +2775,8 @@ gf_status gf_record_spectra(gf_ctx* c, int64_t n, double probe_scale, double* d_
 // ----------------------------------------------------------- training
 size_t gf_mlp_workspace_bytes(int64_t n_rows, int32_t n_samples) {
     if (n_rows < 1 || n_samples < 1) return 0;
-    const size_t nb = (size_t)((n_rows + kBwdBlockRows - 1) / kBwdBlockRows);
+    const size_t nb = (size_t)mlp_bwd_blocks(n_rows);
     size_t o = 0;
-    o = align_up(o + (size_t)n_rows * kMlpH * sizeof(float), kAlign);   // H1
-    o = align_up(o + (size_t)n_rows * kMlpH * sizeof(float), kAlign);   // H2
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);       // O
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);       // dO
     o = align_up(o + nb * kMlpParams * sizeof(float), kAlign);          // block partial gradients
@@ -2788,19 +2786,15 @@ size_t gf_mlp_workspace_bytes(int64_t n_rows, int32_t n_samples) {
 
 namespace {
 struct MlpWs {
-    float *h1, *h2, *o, *dO, *gpart;
+    float *o, *dO, *gpart;
     double* sloss;
     int nb;
 };
 MlpWs carve_mlp(void* ws, int64_t n_rows, int32_t n_samples) {
     MlpWs w;
     unsigned char* b = reinterpret_cast<unsigned char*>(ws);
-    w.nb = (int)((n_rows + kBwdBlockRows - 1) / kBwdBlockRows);
+    w.nb = mlp_bwd_blocks(n_rows);
     size_t o = 0;
-    w.h1 = reinterpret_cast<float*>(b + o);
-    o = align_up(o + (size_t)n_rows * kMlpH * sizeof(float), kAlign);
-    w.h2 = reinterpret_cast<float*>(b + o);
-    o = align_up(o + (size_t)n_rows * kMlpH * sizeof(float), kAlign);
     w.o = reinterpret_cast<float*>(b + o);
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);
     w.dO = reinterpret_cast<float*>(b + o);
@@ -2811,12 +2805,13 @@ MlpWs carve_mlp(void* ws, int64_t n_rows, int32_t n_samples) {
     (void)n_samples;
     return w;
 }
-void raise_mlp_lds() {
-    static bool done = false;
-    if (done) return;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_backward), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kBwdLds);
-    done = true;
+void launch_mlp_forward(const float* params, const float* x, int64_t n_rows, float* out, hipStream_t st) {
+    const int64_t nb = std::min<int64_t>((n_rows + 4 * kMlpRows - 1) / (4 * kMlpRows), kFwdMaxBlocks);
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)nb), dim3(256), 0, st, params, x, n_rows, out);
+}
+AdamStep adam_step(float* params, float* m, float* v, int64_t step, float lr) {
+    return {params, m, v, lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - std::pow(0.9, (double)step)),
+            (float)(1.0 - std::pow(0.999, (double)step))};
 }
 gf_status mlp_status(hipError_t e, const char* what) {
     if (e == hipSuccess) return GF_OK;
@@ -2830,29 +2825,28 @@ gf_status gf_mlp_forward(const float* d_params, const float* d_x, int64_t n_rows
     if (!d_params || !d_x || !d_out || !d_ws || n_rows < 1) return GF_EINVAL;
     if (ws_bytes < gf_mlp_workspace_bytes(n_rows, 1)) return GF_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    MlpWs w = carve_mlp(d_ws, n_rows, 1);
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((n_rows + 255) / 256)), dim3(256), 0, st, d_params, d_x, n_rows,
-                       w.h1, w.h2, d_out);
+    launch_mlp_forward(d_params, d_x, n_rows, d_out, st);
     gf_status s = mlp_status(hipGetLastError(), "mlp forward");
     if (s == GF_OK) s = mlp_status(hipStreamSynchronize(st), "sync");
     return s;
 }
 
-gf_status gf_mlp_loss_grad(const float* d_params, const float* d_x, const float* d_tgt, const int32_t* d_offsets,
-                           int32_t n_samples, int64_t n_rows, float* d_grad, void* d_ws, size_t ws_bytes,
-                           void* stream, double* h_loss) {
+namespace {
+// Loss and gradient, and the optimiser's step on the gradient if step.m is set.
+gf_status mlp_loss_grad(const float* d_params, const float* d_x, const float* d_tgt, const int32_t* d_offsets,
+                        int32_t n_samples, int64_t n_rows, float* d_grad, void* d_ws, size_t ws_bytes, void* stream,
+                        double* h_loss, const AdamStep& step) {
     if (!d_params || !d_x || !d_tgt || !d_offsets || !d_grad || !d_ws || n_rows < 1 || n_samples < 1)
         return GF_EINVAL;
     if (ws_bytes < gf_mlp_workspace_bytes(n_rows, n_samples)) return GF_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     MlpWs w = carve_mlp(d_ws, n_rows, n_samples);
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((n_rows + 255) / 256)), dim3(256), 0, st, d_params, d_x, n_rows,
-                       w.h1, w.h2, w.o);
-    hipLaunchKernelGGL(k_mlp_loss, dim3(n_samples), dim3(256), 0, st, w.o, d_tgt, d_offsets, n_samples, w.dO, w.sloss);
-    raise_mlp_lds();
-    hipLaunchKernelGGL(k_mlp_backward, dim3(w.nb), dim3(256), kBwdLds, st, d_params, d_x, w.h1, w.h2, w.dO, n_rows,
-                       w.gpart);
-    hipLaunchKernelGGL(k_grad_reduce, dim3((kMlpParams + 255) / 256), dim3(256), 0, st, w.gpart, w.nb, d_grad);
+    launch_mlp_forward(d_params, d_x, n_rows, w.o, st);
+    hipLaunchKernelGGL(k_mlp_loss, dim3(n_samples), dim3(kLossThreads), 0, st, w.o, d_tgt, d_offsets, n_samples, w.dO,
+                       w.sloss);
+    hipLaunchKernelGGL(k_mlp_backward, dim3(w.nb), dim3(256), 0, st, d_params, d_x, w.dO, n_rows, w.gpart);
+    hipLaunchKernelGGL(k_grad_reduce, dim3((kMlpParams + kGradParams - 1) / kGradParams),
+                       dim3(kGradParams * kGradSlices), 0, st, w.gpart, w.nb, d_grad, step);
     gf_status s = mlp_status(hipGetLastError(), "mlp loss/gradient");
     if (s == GF_OK && h_loss) {
         std::vector<double> sl(n_samples);
@@ -2865,24 +2859,29 @@ gf_status gf_mlp_loss_grad(const float* d_params, const float* d_x, const float*
     }
     return s;
 }
+}  // namespace
+
+gf_status gf_mlp_loss_grad(const float* d_params, const float* d_x, const float* d_tgt, const int32_t* d_offsets,
+                           int32_t n_samples, int64_t n_rows, float* d_grad, void* d_ws, size_t ws_bytes,
+                           void* stream, double* h_loss) {
+    return mlp_loss_grad(d_params, d_x, d_tgt, d_offsets, n_samples, n_rows, d_grad, d_ws, ws_bytes, stream, h_loss,
+                         AdamStep{});
+}
 
 gf_status gf_mlp_adam(float* d_params, float* d_m, float* d_v, const float* d_grad, int64_t step, float lr,
                       void* stream) {
     if (!d_params || !d_m || !d_v || !d_grad || step < 1 || !(lr > 0.f)) return GF_EINVAL;
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float c1 = (float)(1.0 - std::pow(0.9, (double)step)), c2 = (float)(1.0 - std::pow(0.999, (double)step));
     hipLaunchKernelGGL(k_adam, dim3((kMlpParams + 255) / 256), dim3(256), 0, reinterpret_cast<hipStream_t>(stream),
-                       d_params, d_m, d_v, d_grad, lr, b1, b2, 1e-8f, c1, c2);
+                       d_grad, adam_step(d_params, d_m, d_v, step, lr));
     return mlp_status(hipGetLastError(), "adam");
 }
 
 gf_status gf_mlp_train_step(float* d_params, float* d_m, float* d_v, int64_t step, float lr, const float* d_x,
                             const float* d_tgt, const int32_t* d_offsets, int32_t n_samples, int64_t n_rows,
                             float* d_grad, void* d_ws, size_t ws_bytes, void* stream, double* h_loss) {
-    gf_status s = gf_mlp_loss_grad(d_params, d_x, d_tgt, d_offsets, n_samples, n_rows, d_grad, d_ws, ws_bytes, stream,
-                                   h_loss);
-    if (s != GF_OK) return s;
-    return gf_mlp_adam(d_params, d_m, d_v, d_grad, step, lr, stream);
+    if (!d_params || !d_m || !d_v || step < 1 || !(lr > 0.f)) return GF_EINVAL;
+    return mlp_loss_grad(d_params, d_x, d_tgt, d_offsets, n_samples, n_rows, d_grad, d_ws, ws_bytes, stream, h_loss,
+                         adam_step(d_params, d_m, d_v, step, lr));
 }
 
 int32_t gf_mlp_param_count(void) { return kMlpParams; }

@@ -94,6 +94,42 @@ def test_loss_and_gradient_match_oracle():
     assert np.max(np.abs(got - want)) <= 1e-4 * np.max(np.abs(want))
 
 
+@pytest.mark.parametrize("rows", [(1,), (15,), (17, 47), (64, 1), (20011, 20011)])
+def test_row_groups_and_train_step(rows):
+    """Where the passes' groups of 16 rows and their dealing to the blocks have edges (one row, part groups, more
+    groups than the waves of the largest grid); the bounds of the tests above. The training step gives
+    bitwise the gradient and the optimiser's step of the separate calls."""
+    rng = np.random.default_rng(sum(rows))
+    n, ns = sum(rows), len(rows)
+    x = np.concatenate([rng.uniform(-0.5, 0.5, (n, 4)), rng.uniform(-1, 1, (n, 2))], 1).astype(np.float32)
+    a = rng.uniform(0.1, 2.0, n)
+    b = a * rng.uniform(0.5, 1.5, n)
+    tgt = np.stack([a, b, b * b / a * rng.uniform(1.0, 2.0, n)], 1).astype(np.float32)
+    off = np.cumsum((0,) + rows).astype(np.int32)
+    th = _params(6)
+    nb = gf.gf_mlp_workspace_bytes(n, ns)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda:0")
+    g = torch.empty(gf.gf_mlp_param_count(), dtype=torch.float32, device="cuda:0")
+    th_d, x_d, t_d, o_d = dev(th), dev(x), dev(tgt), dev(off)
+    loss = gf.gf_mlp_loss_grad(th_d.data_ptr(), x_d.data_ptr(), t_d.data_ptr(), o_d.data_ptr(), ns, n, g.data_ptr(),
+                               ws.data_ptr(), nb)
+    samples64 = [(x[i:j].astype(np.float64),) + tuple(tgt[i:j, k].astype(np.float64) for k in range(3))
+                 for i, j in zip(off[:-1], off[1:])]
+    th64 = th.astype(np.float64)
+    assert loss == pytest.approx(mlp.loss(th64, samples64), rel=1e-5)
+    want = mlp.loss_grad(th64, samples64)
+    assert np.max(np.abs(g.cpu().numpy() - want)) <= 1e-4 * np.max(np.abs(want))
+    m0 = (0.1 * rng.standard_normal(th.size)).astype(np.float32)
+    v0 = np.abs(0.1 * rng.standard_normal(th.size)).astype(np.float32)
+    pa, ma, va, pb, mb, vb = dev(th), dev(m0), dev(v0), dev(th), dev(m0), dev(v0)
+    gf.gf_mlp_adam(pa.data_ptr(), ma.data_ptr(), va.data_ptr(), g.data_ptr(), 3, 1e-3)
+    g2 = torch.empty_like(g)
+    gf.gf_mlp_train_step(pb.data_ptr(), mb.data_ptr(), vb.data_ptr(), 3, 1e-3, x_d.data_ptr(), t_d.data_ptr(),
+                         o_d.data_ptr(), ns, n, g2.data_ptr(), ws.data_ptr(), nb)
+    torch.cuda.synchronize()
+    assert torch.equal(g, g2) and torch.equal(pa, pb) and torch.equal(ma, mb) and torch.equal(va, vb)
+
+
 def test_adam_step_matches_oracle():
     rng = np.random.default_rng(5)
     n = gf.gf_mlp_param_count()
