@@ -124,14 +124,17 @@ __global__ void __launch_bounds__(1024) k_wcorr_xy_fwd(cx<double>* __restrict__ 
     for (int i = threadIdx.x; i < ny; i += nthr) twy[i] = twgy[i];
     const int plane = nx * ny;
     cx<double>* g = W + (size_t)blockIdx.y * wps + (size_t)blockIdx.x * plane;
+    const SmallDiv by_nx(nx);
     for (int e = threadIdx.x; e < plane; e += nthr) {
-        const int y = e / nx, x = e - y * nx;
+        int y, x;
+        by_nx.split(e, y, x);
         buf[y * rs + x] = g[e];
     }
     __syncthreads();
     wcorr_plane_fft<EPT>(buf, twx, twy, px, py, nx, ny, rs, false);
     for (int e = threadIdx.x; e < plane; e += nthr) {
-        const int y = e / nx, x = e - y * nx;
+        int y, x;
+        by_nx.split(e, y, x);
         g[e] = buf[y * rs + x];
     }
 }
@@ -151,9 +154,11 @@ __global__ void __launch_bounds__(1024) k_wcorr_z(const cx<double>* __restrict__
     const int nthr = blockDim.x;
     for (int i = threadIdx.x; i < nz; i += nthr) twz[i] = twgz[i];
     const int q0 = blockIdx.x * bx;
+    const SmallDiv by_e(E), by_bx(bx);
     for (int e = threadIdx.x; e < 9 * E; e += nthr) {
-        const int f = e / E, r = e - f * E;
-        const int z = r / bx, b = r - z * bx;
+        int f, r, z, b;
+        by_e.split(e, f, r);
+        by_bx.split(r, z, b);
         buf[e] = W[(size_t)f * wps + (size_t)z * plane + q0 + b];
     }
     __syncthreads();
@@ -167,7 +172,8 @@ __global__ void __launch_bounds__(1024) k_wcorr_z(const cx<double>* __restrict__
     __syncthreads();
     fft_rows<EPT, double, true>(sb, twz, pz, bx, bx, bx, 1, 0);
     for (int e = threadIdx.x; e < E; e += nthr) {
-        const int z = e / bx, b = e - z * bx;
+        int z, b;
+        by_bx.split(e, z, b);
         Sg[(size_t)z * plane + q0 + b] = sb[e];
     }
 }
@@ -187,15 +193,18 @@ __global__ void __launch_bounds__(1024) k_wcorr_xy_inv(const cx<double>* __restr
     for (int i = threadIdx.x; i < ny; i += nthr) twy[i] = twgy[i];
     const int plane = nx * ny;
     const cx<double>* g = Sg + (size_t)blockIdx.x * plane;
+    const SmallDiv by_nx(nx);
     for (int e = threadIdx.x; e < plane; e += nthr) {
-        const int y = e / nx, x = e - y * nx;
+        int y, x;
+        by_nx.split(e, y, x);
         buf[y * rs + x] = g[e];
     }
     __syncthreads();
     wcorr_plane_fft<EPT>(buf, twx, twy, px, py, nx, ny, rs, true);
     double* out = corr + (size_t)blockIdx.x * plane;
     for (int e = threadIdx.x; e < plane; e += nthr) {
-        const int y = e / nx, x = e - y * nx;
+        int y, x;
+        by_nx.split(e, y, x);
         out[e] = buf[y * rs + x].re * scale;
     }
 }
