@@ -39,7 +39,7 @@ def kernel_bytes(name, vol, L, S, nblk):
     field = W * S * vol
     gauge = 12 * S * vol  # rows 1-2 of a transform
     return {
-        "update_measure": links + gauge + field,  # read U0 and H; write Delta
+        "update_measure": links + gauge + field,  # read U0 and H; write Delta or its (x, y) transform
         "divergence": links + gauge + field,      # the same kernel as a standalone measurement
         "update": 2 * gauge + field,              # read (alpha/2)Delta~ and H, write H
         "fft_xy_fwd": 2 * field,
@@ -49,11 +49,12 @@ def kernel_bytes(name, vol, L, S, nblk):
     }[name]
 
 
-def iteration_bytes_per_site(L, S):
+def iteration_bytes_per_site(L, S, joined=False):
     """Algorithmic bytes per site of one whole FA iteration as the library stores the links (U0 and H):
-    the three FFT passes, the gauge update of H and the loop kernel."""
+    the three FFT passes, the gauge update of H and the loop kernel (joined: which leaves the forward
+    (x, y) transform itself)."""
     W = 8
-    return (2 * W + 2 * W + (W + 24) + (4 * L + 12 + W)) * S
+    return ((0 if joined else 2 * W) + 2 * W + (W + 24) + (4 * L + 12 + W)) * S
 
 
 STORAGE = {"fp64_18": (18, 8), "fp64_12": (12, 8), "fp32_12": (12, 4), "fp32_18": (18, 4)}
@@ -62,16 +63,20 @@ STORAGE = {"fp64_18": (18, 8), "fp64_12": (12, 8), "fp32_12": (12, 4), "fp32_18"
 PMC_PROFILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles",
                            "update_measure_{prec}_{dims}_pmc.md")
 KERNEL_SOURCES = ["paper_1208_1186_amd/csrc/gf_device.hpp", "paper_1208_1186_amd/csrc/gf_kernels.hpp"]
+# the loop kernel that also takes the forward (x, y) transform has counter summaries of its own
+JOINED_PROFILE = PMC_PROFILE.replace("update_measure_", "measure_xy_")
+JOINED_SOURCES = KERNEL_SOURCES + ["paper_1208_1186_amd/csrc/gf_fft.hpp", "paper_1208_1186_amd/csrc/gf_fft_ct.hpp",
+                                   "paper_1208_1186_amd/csrc/gf_join.hpp"]
 
 
-def kernel_source_digest(root=None):
+def kernel_source_digest(root=None, sources=None):
     """sha256 of the loop kernel's sources with comments and blank lines removed: the code the committed
     counter summaries were taken on (a comment edit leaves it unchanged)."""
     import hashlib
     import re
     root = root or os.path.dirname(os.path.abspath(__file__))
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES:
+    for f in sources or KERNEL_SOURCES:
         text = open(os.path.join(root, f)).read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
         text = re.sub(r"//[^\n]*", "", text)
@@ -79,17 +84,17 @@ def kernel_source_digest(root=None):
     return h.hexdigest()
 
 
-def counted_traffic(prec, dims, traversal=None):
+def counted_traffic(prec, dims, traversal=None, joined=False):
     """HBM bytes per launch of the loop kernel from the committed rocprofv3 FETCH/WRITE passes, scaled by
     the copy calibration; None if there is no such profile or the kernel code changed since. The
     traversal's own counter lines (`fetch_kib_per_dispatch_z<traversal>:`) are taken when the profile
-    has them, else the generic ones."""
+    has them, else the generic ones. joined: the loop kernel that includes the forward (x, y) transform."""
     import re
-    path = PMC_PROFILE.format(prec=prec, dims="x".join(str(d) for d in dims))
+    path = (JOINED_PROFILE if joined else PMC_PROFILE).format(prec=prec, dims="x".join(str(d) for d in dims))
     if not os.path.exists(path):
         return None
     text = open(path).read()
-    if kernel_source_digest() not in text:
+    if kernel_source_digest(sources=JOINED_SOURCES if joined else None) not in text:
         return None
     vals = {}
     for key in ["fetch_scale", "write_scale", "fetch_kib_per_dispatch", "write_kib_per_dispatch"]:
@@ -618,7 +623,9 @@ def main():
     avg_dom = ms_dom / n_dom
     by_dom = kernel_bytes(dom, vol, L, S, nblk)
     achieved = round(by_dom / (avg_dom * 1e-3) / 1e9, 1)
-    traffic = counted_traffic(prec, dims, TILINGS.get(prec, (None,) * 3)[2]) if dom == "update_measure" else None
+    joined = "fft_xy_fwd" not in kern
+    traffic = (counted_traffic(prec, dims, TILINGS.get(prec, (None,) * 3)[2], joined)
+               if dom == "update_measure" else None)
     roofline = {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "bytes_per_launch": by_dom, "avg_launch_ms": round(avg_dom, 5), "launches_timed": n_dom}
@@ -743,8 +750,8 @@ def main():
         "hbm_model_GBps": round(b_alg * vol * rate / 1e9, 1),
         "hbm_model_frac": round(b_alg * vol * rate / 1e9 / HBM_PEAK_GBS, 4),
         "hbm_model_bytes_per_site": b_alg,
-        "iteration_bytes_per_site": iteration_bytes_per_site(L, S),
-        "iteration_GBps": round(iteration_bytes_per_site(L, S) * vol * rate / 1e9, 1),
+        "iteration_bytes_per_site": iteration_bytes_per_site(L, S, joined),
+        "iteration_GBps": round(iteration_bytes_per_site(L, S, joined) * vol * rate / 1e9, 1),
         "roofline": roofline,
         "cpu_baseline": cpu,
         "kernels": kern,

@@ -309,13 +309,13 @@ gf_status gf_stage_update(gf_ctx* ctx, const void* d_scaled);
  * duration in milliseconds and the number of launches timed.
  */
 enum {
-    GF_K_FFT_XY_FWD = 0,  /* forward 2D FFT over (x, y) */
+    GF_K_FFT_XY_FWD = 0,  /* forward 2D FFT over (x, y) (no launch where the loop kernel includes it) */
     GF_K_FFT_ZT = 1,      /* 2D FFT over (z, t), filter, inverse (z, t) */
     GF_K_FFT_XY_INV = 2,  /* inverse 2D FFT over (x, y) (in the loop: followed by g(x)) */
     GF_K_UPDATE = 3,      /* single-stage update U_mu(x) -> g(x) U_mu(x) g(x+mu)^dag */
     GF_K_DIVERGENCE = 4,  /* standalone Delta(x) and block partial sums of F, theta */
     GF_K_FINALIZE = 5,    /* fixed-order reduction -> theta, F, stop flag */
-    GF_K_UPDATE_MEASURE = 6,  /* loop kernel: update, divergence of the new links, reduction */
+    GF_K_UPDATE_MEASURE = 6,  /* loop kernel: divergence of the new links (on some planes its (x, y) FFT), sums */
     GF_NKERNELS = 8
 };
 gf_status gf_set_timing(gf_ctx* ctx, int32_t enable);

@@ -27,6 +27,7 @@
 #include "../../include/gf.h"
 #include "gf_fft_ct.hpp"
 #include "gf_fft_reg.hpp"
+#include "gf_join.hpp"
 #include "gf_batch.hpp"
 #include "gf_kernels.hpp"
 
@@ -85,7 +86,10 @@ struct Layout {
     int nblk;         // blocks of the one-site-per-thread kernels
     int nblk_fused;   // blocks of the loop kernel (kFusedSites sites each)
     int zb = 1;       // loop-kernel traversal: z planes per group inside the t loop, 0: blocks step
-                      // through t, -1: bricks step through t segments (autotuned)
+                      // through t, -1: bricks step through t segments (autotuned); the order of the
+                      // planes where strips > 0
+    int strips = 0;   // strips per (z, t) plane of the loop kernel that also transforms in (x, y) (k_measure_xy),
+                      // 0: the shape takes k_update_measure and a forward (x, y) pass
     BrickGeom bk{};   // brick march geometry (bk.by == 0: the shape has none)
     int bk_threads = 0;
     bool fp32;
@@ -149,6 +153,8 @@ int zt_reg_bx(const Layout& L) {
 }
 
 void plan_brick(Layout& L);
+int join_strips(const Layout& L);
+std::vector<int> zt_candidates(const Layout& L);
 
 gf_status plan_plain(const gf_params* p, Layout& L, std::string& err) {
     if (!p) {
@@ -218,6 +224,7 @@ gf_status plan_plain(const gf_params* p, Layout& L, std::string& err) {
         return GF_ENOTSUP;
     }
     if (const int rb = zt_reg_bx(L)) L.bx = rb;  // the register pass of this shape
+    if ((p->flags & (GF_FLAG_GENERIC_FFT | GF_FLAG_BATCH_FUSED)) == 0) L.strips = join_strips(L);
     set_zt_tile(L, L.bx);
     // inverse (x, y) + gauge pass: the four fields of one (z, t) plane per block.
     const int EC = 4 * nx * ny;
@@ -311,6 +318,9 @@ struct gf_ctx {
     void* tw[4];
     void* D;      // divergence of the current links (four packed fields)
     void* Q;      // FFT work buffer (four packed fields)
+    // L.strips > 0: Q holds the forward (x, y) transform of the current links' divergence, as the last
+    // measurement left it (every other use of Q clears this, and so does a stopped loop)
+    bool q_valid = false;
     void* U0;     // the input links (SoA planes)
     void* Hb[2];  // accumulated gauge transform rows after k updates in Hb[k & 1]
     // learned preconditioner state
@@ -475,16 +485,29 @@ bool launch_xy_ct(gf_ctx* c, const void* src, void* dst, int force, bool loop_re
 }
 
 
+// Partials that the loop kernel leaves: one per plane, or per 64 sites.
+int loop_partials(const Layout& L) { return L.strips ? L.n[2] * L.n[3] : L.nblk_fused; }
+
+// Reduction of the loop kernel's partials, if they are still pending.
+void queue_finalize(gf_ctx* c) {
+    tstart(c, GF_K_FINALIZE);
+    hipLaunchKernelGGL(k_finalize, dim3(1, c->nact), dim3(256), 0, c->st, c->part, loop_partials(c->L), inv3v(c),
+                       inv12v(c), c->ctl, 1, bt(c));
+    tstop(c);
+}
+
 template <typename T>
-bool launch_zt_ct(gf_ctx* c, void* Z, T coef, int no_fa, int force, const T* mtab, cx<T>* spec) {
+bool launch_zt_ct(gf_ctx* c, void* Z, T coef, int no_fa, int force, const T* mtab, cx<T>* spec, bool loop_reduce) {
     const Layout& L = c->L;
+    const double2* part = loop_reduce ? c->part : nullptr;
+    const int np = loop_partials(L), red = loop_reduce ? 1 : 0;
     const T* s2 = reinterpret_cast<const T*>(c->sin2);
 #define GF_X(A, B, BB)                                                                                     \
     if (L.n[2] == A && L.n[3] == B && L.n[0] % BB == 0) {                                                  \
-        hipLaunchKernelGGL((k_fft_zt_reg<T, A, B, BB>), dim3(4 * L.n[1] * (L.n[0] / BB), c->nact),          \
+        hipLaunchKernelGGL((k_fft_zt_reg<T, A, B, BB>), dim3(4 * L.n[1] * (L.n[0] / BB) + red, c->nact),    \
                            dim3(BB * (A > B ? A : B)), 0, c->st, cxp<T>(Z), L.ps, L.n[0], L.n[1],          \
                            twp<T>(c, 2), twp<T>(c, 3), s2, coef, no_fa, c->ctl, force, mtab, c->tg, spec,  \
-                           bt(c));                                                                         \
+                           part, np, inv3v(c), inv12v(c), bt(c));                                          \
         return true;                                                                                       \
     }
     if constexpr (sizeof(T) == 8) {
@@ -496,10 +519,10 @@ bool launch_zt_ct(gf_ctx* c, void* Z, T coef, int no_fa, int force, const T* mta
     if (L.n[0] > kZtMaxXY || L.n[1] > kZtMaxXY) return false;
 #define GF_X(A, B, BB)                                                                                     \
     if (L.n[2] == A && L.n[3] == B && L.bx == BB) {                                                        \
-        hipLaunchKernelGGL((k_fft_zt_ct<T, A, B, BB>), dim3(4 * L.n[1] * (L.n[0] / BB), c->nact),           \
+        hipLaunchKernelGGL((k_fft_zt_ct<T, A, B, BB>), dim3(4 * L.n[1] * (L.n[0] / BB) + red, c->nact),     \
                            dim3(ct_threads(BB * A * B, 8)), 0, c->st, cxp<T>(Z), L.ps, L.n[0], L.n[1],     \
                            twp<T>(c, 2), twp<T>(c, 3), s2, coef, no_fa, c->ctl, force, mtab, c->tg, spec,  \
-                           bt(c));                                                                         \
+                           part, np, inv3v(c), inv12v(c), bt(c));                                          \
         return true;                                                                                       \
     }
     if constexpr (sizeof(T) == 8) {
@@ -555,15 +578,18 @@ void launch_xy(gf_ctx* c, const void* src, void* dst, int force, bool loop_reduc
     tstop(c);
 }
 
+// (z, t) pass with the filter, in place on Z (= Q). With loop_reduce (the joined loop's first launch) block 0
+// also reduces pending loop partials.
 template <typename T>
-void launch_zt(gf_ctx* c, void* Z, int force) {
+void launch_zt(gf_ctx* c, void* Z, int force, bool loop_reduce = false) {
     const Layout& L = c->L;
+    c->q_valid = false;
     const bool no_fa = (c->p.flags & GF_FLAG_NO_FA) != 0;
     const double coef = 0.5 * c->p.alpha * (no_fa ? 1.0 : 16.0) / (double)L.vol * c->coef_scale;
     tstart(c, GF_K_FFT_ZT);
     const T* mtab = c->net_this ? reinterpret_cast<const T*>(c->mtab) : nullptr;
     cx<T>* spec = reinterpret_cast<cx<T>*>(c->spec_capture);
-    if (!generic_fft(c) && launch_zt_ct<T>(c, Z, (T)coef, no_fa ? 1 : 0, force, mtab, spec)) {
+    if (!generic_fft(c) && launch_zt_ct<T>(c, Z, (T)coef, no_fa ? 1 : 0, force, mtab, spec, loop_reduce)) {
         tstop(c);
         return;
     }
@@ -673,16 +699,91 @@ void launch_loop_kernel(gf_ctx* c, const void* h, int force, Ctl* ctl, void* dst
                        force);
 }
 
-// Standalone measurement of the current links (transform in buffer k & 1): Delta -> D, theta and F.
+// Plane shapes whose loop kernel also takes the forward (x, y) transform (Nx, Ny, strips per plane; threads: two
+// per column and strip), and the numbers of planes from which (in double, in float) and up to which it is the
+// faster form. Per update, both launches -> joined (us), measured on each side of these lines: 8 x 8 from 64 planes
+// on 18.2 -> 15.6 (8^4), level at 144, 25 -> 22 at 384; 16 x 16 at 64 planes 22.8 -> 24.0, level at 144, 31.0 -> 27.7
+// at 192, 33.3 -> 30.7 (FP64-18), 34.6 -> 29.2 (FP64-12) and 28.3 -> 24.3 (FP32-12) at 256; 32 x 32 in double
+// at 192 60.9 -> 62.7, at 256 73.2 -> 72.5 (FP64-12 78 -> 67.7), at 384 119 -> 113, in float at 256 45.4 -> 47.9,
+// at 384 60.5 -> 58.5; 12 x 12 in float 21.1 -> 20.6 at 64 planes, 24.5 -> 23.3 at 144, 29.2 -> 27.4 at 384,
+// 37.1 -> 38.0 at 1024, in double 22.5 -> 23.6, 27.5 -> 27.2, 34.5 -> 39.0 and 52 -> 69 (five waves to a block, of
+// which two or three fit a CU). 24 x 24 and 48 x 48 planes leave LDS for a block or two per CU: 24.5 -> 26 and
+// 191 -> 217 for the two kernels.
+constexpr int kJoinAny = 1 << 30;
+#define GF_JOIN_CASES(X)                \
+    X(8, 8, 8, 1, 1, kJoinAny)          \
+    X(12, 12, 12, kJoinAny, 1, 512)     \
+    X(16, 16, 8, 128, 128, kJoinAny)    \
+    X(32, 32, 4, 256, 384, kJoinAny)
+
+// Strips of this shape, or 0 for the two launches: the rule above, a compiled (z, t) tiling (those kernels can
+// reduce the partials) and links under 4 GiB (32-bit offsets). The choice looks at the extents and the
+// precision only: a lattice of a batch sums its partials as it does alone.
+int join_strips(const Layout& L) {
+    if ((size_t)4 * L.ne * L.ps * (L.fp32 ? 8 : 16) >= ((size_t)1 << 32)) return 0;
+    const std::vector<int> zt = zt_candidates(L);
+    if (std::find(zt.begin(), zt.end(), L.bx) == zt.end()) return 0;
+    const int planes = L.n[2] * L.n[3];
+#define GF_X(A, B, S, LO64, LO32, HI) \
+    if (L.n[0] == A && L.n[1] == B && planes >= (L.fp32 ? LO32 : LO64) && planes <= HI) return S;
+    GF_JOIN_CASES(GF_X)
+#undef GF_X
+    return 0;
+}
+
+// The kernel of a shape, or null where the precision never takes it.
+template <typename T, int NE, int A, int B, int S, int LO64, int LO32>
+constexpr auto join_kernel() {
+    if constexpr ((sizeof(T) == 8 ? LO64 : LO32) < kJoinAny)
+        return &k_measure_xy<T, NE, A, B, S>;
+    else
+        return nullptr;
+}
+
 template <typename T, int NE>
-void launch_measure_t(gf_ctx* c) {
+void launch_join(gf_ctx* c, const void* h, int force, Ctl* ctl, int nact) {
+    const Layout& L = c->L;
+#define GF_X(A, B, S, LO64, LO32, HI)                                                                                \
+    if constexpr (constexpr auto kern = join_kernel<T, NE, A, B, S, LO64, LO32>(); kern != nullptr) {                \
+        if (L.n[0] == A && L.n[1] == B) {                                                                            \
+            hipLaunchKernelGGL(kern, dim3(L.n[2] * L.n[3], nact), dim3(join_threads(A, S)),                          \
+                               join_lds(A, B, sizeof(cx<T>)), c->st, links_of<T, NE>(c),                             \
+                               reinterpret_cast<const cx<T>*>(h), cxp<T>(c->Q), L.ps, L.n[2], L.n[3], twp<T>(c, 0),  \
+                               twp<T>(c, 1), c->part, ctl, bt(c), L.zb, force);                                      \
+            return;                                                                                                  \
+        }                                                                                                            \
+    }
+    GF_JOIN_CASES(GF_X)
+#undef GF_X
+}
+
+template <typename T, int NE>
+void raise_lds_join() {
+#define GF_X(A, B, S, LO64, LO32, HI)                                                              \
+    if constexpr (constexpr auto kern = join_kernel<T, NE, A, B, S, LO64, LO32>(); kern != nullptr) \
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                             \
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+    GF_JOIN_CASES(GF_X)
+#undef GF_X
+}
+
+// Measurement of the current links (transform in buffer k & 1): theta and F, and Delta -> D or, where the loop
+// kernel transforms (and the divergence itself is not asked for), its (x, y) transform -> Q.
+template <typename T, int NE>
+void launch_measure_t(gf_ctx* c, bool want_d) {
+    const bool join = c->L.strips != 0 && !want_d;
     tstart(c, GF_K_DIVERGENCE);
-    launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->ctl, c->D, 1);
+    if (join)
+        launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->ctl, 1);
+    else
+        launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->ctl, c->D, 1);
     tstop(c);
     tstart(c, GF_K_FINALIZE);
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, c->st, c->part, c->L.nblk_fused, inv3v(c), inv12v(c),
-                       c->ctl, 0, Batch{nullptr, 0});
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, c->st, c->part,
+                       join ? loop_partials(c->L) : c->L.nblk_fused, inv3v(c), inv12v(c), c->ctl, 0,
+                       Batch{nullptr, 0});
     tstop(c);
+    if (join) c->q_valid = true;
 }
 
 // Update of the current links from (alpha/2) Delta~ packed in Q: H <- reunitarize(g H) in place.
@@ -695,11 +796,16 @@ void launch_update_t(gf_ctx* c) {
     tstop(c);
 }
 
-// Loop kernel after update k (transform of k + 1 updates): divergence -> D, partials.
+// Loop kernel after update k (transform of k + 1 updates): divergence -> D or its transform -> Q, partials.
 template <typename T, int NE>
 void launch_fused_t(gf_ctx* c, long long k) {
     tstart(c, GF_K_UPDATE_MEASURE);
-    launch_loop_kernel<T, NE>(c, c->Hb[(k + 1) & 1], 0, c->ctl, c->D, c->nact);
+    if (c->L.strips) {
+        launch_join<T, NE>(c, c->Hb[(k + 1) & 1], 0, c->ctl, c->nact);
+        c->q_valid = true;  // unless the loop has stopped: the caller looks when it reads the control block
+    } else {
+        launch_loop_kernel<T, NE>(c, c->Hb[(k + 1) & 1], 0, c->ctl, c->D, c->nact);
+    }
     tstop(c);
 }
 
@@ -725,41 +831,46 @@ void launch_unpack_t(gf_ctx* c, double* dst) {
 
 gf_status launched(gf_ctx* c, const char* what) { return check_hip(c, hipGetLastError(), what); }
 
-gf_status launch_measure(gf_ctx* c) {
-    GF_DISPATCH(c, launch_measure_t, c);
+gf_status launch_measure(gf_ctx* c, bool want_d = false) {
+    GF_DISPATCH(c, launch_measure_t, c, want_d);
     return launched(c, "divergence launch");
+}
+
+// Before the first of a run of updates: Q as they expect it.
+gf_status ensure_transform(gf_ctx* c) { return c->L.strips == 0 || c->q_valid ? GF_OK : launch_measure(c); }
+
+gf_status loop_finalize(gf_ctx* c) {
+    queue_finalize(c);
+    return launched(c, "finalize launch");
+}
+
+// The passes of the update from k to k + 1: forward transform and filter, the inverse with the gauge step. The
+// forward (x, y) transform is in Q already where the loop kernel forms it; the partials of the loop kernel
+// before are then reduced beside the (z, t) pass, or on their own ahead of the network's table, which reads
+// theta.
+template <typename T>
+void update_passes(gf_ctx* c, long long k) {
+    const bool join = c->L.strips != 0;
+    if (!join) launch_xy<T, false>(c, c->D, c->Q, 0, true);
+    if (c->net_this) {
+        if (join) queue_finalize(c);
+        const double coef = 0.5 * c->p.alpha * 16.0 / (double)c->L.vol;
+        hipLaunchKernelGGL(k_mlp_table<T>, dim3((c->L.ntuples + kTableTuplesPerBlock - 1) / kTableTuplesPerBlock),
+                           dim3(256), 0, c->st, c->mlp, reinterpret_cast<const T*>(c->sin2), c->tg, coef, c->ctl, 0,
+                           reinterpret_cast<T*>(c->mtab));
+    }
+    launch_zt<T>(c, c->Q, 0, join);
+    launch_gauge_pass<T>(c, 0, c->Hb[k & 1], c->Hb[(k + 1) & 1]);
 }
 
 // Queue the update from k to k + 1 (no-ops on the device once the stop flag is set).
 gf_status one_iteration(gf_ctx* c, long long k) {
-    const double coef = 0.5 * c->p.alpha * 16.0 / (double)c->L.vol;
-    if (c->L.fp32) {
-        launch_xy<float, false>(c, c->D, c->Q, 0, true);
-        if (c->net_this)
-            hipLaunchKernelGGL(k_mlp_table<float>, dim3((c->L.ntuples + kTableTuplesPerBlock - 1) / kTableTuplesPerBlock), dim3(256), 0, c->st, c->mlp,
-                               reinterpret_cast<const float*>(c->sin2), c->tg, coef, c->ctl, 0,
-                               reinterpret_cast<float*>(c->mtab));
-        launch_zt<float>(c, c->Q, 0);
-        launch_gauge_pass<float>(c, 0, c->Hb[k & 1], c->Hb[(k + 1) & 1]);
-    } else {
-        launch_xy<double, false>(c, c->D, c->Q, 0, true);
-        if (c->net_this)
-            hipLaunchKernelGGL(k_mlp_table<double>, dim3((c->L.ntuples + kTableTuplesPerBlock - 1) / kTableTuplesPerBlock), dim3(256), 0, c->st, c->mlp,
-                               reinterpret_cast<const double*>(c->sin2), c->tg, coef, c->ctl, 0,
-                               reinterpret_cast<double*>(c->mtab));
-        launch_zt<double>(c, c->Q, 0);
-        launch_gauge_pass<double>(c, 0, c->Hb[k & 1], c->Hb[(k + 1) & 1]);
-    }
+    if (c->L.fp32)
+        update_passes<float>(c, k);
+    else
+        update_passes<double>(c, k);
     GF_DISPATCH(c, launch_fused_t, c, k);
     return launched(c, "loop launch");
-}
-
-gf_status loop_finalize(gf_ctx* c) {
-    tstart(c, GF_K_FINALIZE);
-    hipLaunchKernelGGL(k_finalize, dim3(1, c->nact), dim3(256), 0, c->st, c->part, c->L.nblk_fused, inv3v(c),
-                       inv12v(c), c->ctl, 1, bt(c));
-    tstop(c);
-    return launched(c, "finalize launch");
 }
 
 gf_status read_head(gf_ctx* c) {
@@ -767,6 +878,7 @@ gf_status read_head(gf_ctx* c) {
     GF_TRY_HIP(c, hipStreamSynchronize(c->st));
     if (c->npend) tdrain(c);
     c->k_host = c->h_head->iters;
+    if (c->h_head->done) c->q_valid = false;  // a pass may have been under way when the loop stopped
     return GF_OK;
 }
 
@@ -815,6 +927,10 @@ void raise_lds_limits() {
     raise_lds_brick<double, 6>();
     raise_lds_brick<float, 9>();
     raise_lds_brick<float, 6>();
+    raise_lds_join<double, 9>();
+    raise_lds_join<double, 6>();
+    raise_lds_join<float, 9>();
+    raise_lds_join<float, 6>();
     (void)hipGetLastError();
     done = true;
 }
@@ -861,6 +977,7 @@ void gauge_unpack(gf_ctx* c, const void* rows, void* dst) {
 // g itself (rows 1-2) to gauge.
 template <typename T>
 void stage_spectral(gf_ctx* c, void* gauge) {
+    c->q_valid = false;
     launch_xy<T, false>(c, c->Q, c->Q, 1, false);
     launch_zt<T>(c, c->Q, 1);
     if (gauge)
@@ -977,8 +1094,13 @@ std::vector<int> zb_candidates(const Layout& L) {
 
 template <typename T, int NE>
 void time_loop_t(gf_ctx* c, double& ms_out) {
-    // trial launches on the current links: divergence -> Q, partials of a scratch control-block head
-    ms_out = time_launches(c, [&]() { launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->Q, 1); });
+    // trial launches on the current links: divergence or transform -> Q, partials of a scratch control-block head
+    ms_out = time_launches(c, [&]() {
+        if (c->L.strips)
+            launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, 1);
+        else
+            launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->Q, 1);
+    });
 }
 
 gf_status autotune(gf_ctx* c) {
@@ -1013,11 +1135,12 @@ gf_status autotune(gf_ctx* c) {
             }
         bestv = cand[std::min_element(t.begin(), t.end()) - t.begin()];
     };
-    if (xs.size() > 1) pick(xs, true, bestG);
+    if (xs.size() > 1 && c->L.strips == 0) pick(xs, true, bestG);  // (no forward (x, y) pass in a joined loop)
     set_xy_tile(c->L, bestG);
     if (zs.size() > 1) pick(zs, false, bestB);
     set_zt_tile(c->L, bestB);
     int bestZ = 1;
+    c->q_valid = false;
     const std::vector<int> zbs = zb_candidates(c->L);
     if (zbs.size() > 1) {
         // trial launches write Q, the block partials and a scratch control-block head; D, the control
@@ -1086,6 +1209,11 @@ gf_status run_loop(gf_ctx* c, double tol, int64_t max_iter, gf_result* r, bool u
     if (s == GF_OK) s = read_head(c);
     if (s != GF_OK) return s;
     const long long start = c->h_head->iters;
+    if (c->L.strips && !c->q_valid && !c->h_head->done && max_iter > 0) {
+        s = launch_measure(c);
+        if (s == GF_OK) s = read_head(c);
+        if (s != GF_OK) return s;
+    }
     while (!c->h_head->done && c->h_head->iters - start < max_iter) {
         const int64_t left = max_iter - (c->h_head->iters - start);
         int64_t k = std::min<int64_t>(left, c->p.check_every);
@@ -1216,6 +1344,7 @@ gf_status init_plain(gf_ctx* c, const gf_params& p, const Layout& L, double* d_l
     }
     if (s == GF_OK && measure) s = launch_measure(c);
     if (s == GF_OK) s = autotune(c);
+    if (s == GF_OK && measure) s = ensure_transform(c);  // the trial launches wrote over Q
     if (shared) return s;
     if (s == GF_OK) s = read_head(c);
     if (s == GF_OK) {
@@ -1712,6 +1841,7 @@ gf_status finish_gather(gf_ctx* c, BatchGroup& g) {
         gf_ctx* v = g.view[g.ph][i];
         std::memcpy(v->h_head, g.h_heads + (size_t)i * kHeadBytes, kHeadBytes);
         v->k_host = v->h_head->iters;
+        if (v->h_head->done) v->q_valid = false;  // as in read_head
     }
     return GF_OK;
 }
@@ -1747,8 +1877,12 @@ gf_status advance_group(gf_ctx* c, BatchGroup& g, double tol, std::vector<BatchO
     gf_status s = GF_OK;
     switch (g.stage) {
         case BatchGroup::kStart:  // arm the stopping test of the phase, then read every control block
-            for (int i = 0; i < ng && s == GF_OK; ++i)
-                if (!out[g.idx[i]].finished) s = set_tol(g.view[g.ph][i], phase_tol(c, g, tol));
+            for (int i = 0; i < ng && s == GF_OK; ++i) {
+                if (out[g.idx[i]].finished) continue;
+                gf_ctx* v = g.view[g.ph][i];
+                s = ensure_transform(v);
+                if (s == GF_OK) s = set_tol(v, phase_tol(c, g, tol));
+            }
             if (s == GF_OK) s = enqueue_gather(c, g);
             return s;
         case BatchGroup::kRun: {  // one chunk of updates over the active configurations
@@ -2490,6 +2624,9 @@ gf_status gf_set_state(gf_ctx* c, const void* d_in, size_t bytes) {
         return fail(c, GF_EINVAL, "state was not saved from a context with these parameters");
     GF_TRY_HIP(c, hipMemcpyAsync(c->ws, in + kStateHead, c->L.total, hipMemcpyDeviceToDevice, c->st));
     restore_header(c, h);
+    c->q_valid = false;  // (a state may have been saved between stage calls)
+    for (gf_ctx* k : c->child)
+        if (k) k->q_valid = false;
     gf_ctx* a = active(c);
     gf_status st = read_head(a);
     if (st == GF_OK) st = unpack_links(a, c->links_user);
@@ -2523,7 +2660,7 @@ gf_status gf_stage_divergence(gf_ctx* c, void* d_delta) {
     if (c->batch) return fail(c, GF_ESTATE, "a batch context only takes the batch calls");
     if (c->L.mixed) c = active(c);
     if (!d_delta) return fail(c, GF_EINVAL, "d_delta is NULL");
-    gf_status s = launch_measure(c);
+    gf_status s = launch_measure(c, true);
     if (s != GF_OK) return s;
     if (c->L.fp32)
         field_unpack<float>(c, c->D, d_delta);
@@ -2583,6 +2720,7 @@ gf_status gf_stage_update(gf_ctx* c, const void* d_scaled) {
         field_pack<float>(c, d_scaled, c->Q);
     else
         field_pack<double>(c, d_scaled, c->Q);
+    c->q_valid = false;
     GF_DISPATCH(c, launch_update_t, c);
     gf_status s = launched(c, "update launch");
     if (s == GF_OK) s = unpack_links(c, c->links_user);
@@ -2709,13 +2847,15 @@ gf_status gf_record_spectra(gf_ctx* c, int64_t n, double probe_scale, double* d_
     if (s == GF_OK) s = read_head(c);
     const long long k0 = c->k_host;
     const size_t recn = (size_t)c->L.ntuples * 3;
-    auto forward_passes = [&]() {  // spectrum of D into spec_capture (forward (x, y) and (z, t) passes into Q)
+    if (s == GF_OK) s = ensure_transform(c);
+    const bool join = c->L.strips != 0;
+    auto forward_passes = [&]() {  // spectrum of the divergence into spec_capture (forward passes into Q)
         if (c->L.fp32) {
-            launch_xy<float, false>(c, c->D, c->Q, 1, true);
-            launch_zt<float>(c, c->Q, 1);
+            if (!join) launch_xy<float, false>(c, c->D, c->Q, 1, true);
+            launch_zt<float>(c, c->Q, 1, join);
         } else {
-            launch_xy<double, false>(c, c->D, c->Q, 1, true);
-            launch_zt<double>(c, c->Q, 1);
+            if (!join) launch_xy<double, false>(c, c->D, c->Q, 1, true);
+            launch_zt<double>(c, c->Q, 1, join);
         }
         return launched(c, "spectrum launch");
     };

@@ -113,13 +113,16 @@ constexpr int kZtMaxXY = 64;
 
 // (z, t) pass with the filter, BX x columns per block, in place. The first z stage reads the
 // columns from memory and the last inverse z stage writes them back; the filter and the first
-// inverse t stage work on the last forward t stage's registers.
+// inverse t stage work on the last forward t stage's registers. With part set (one more block), block 0
+// only reduces the loop kernel's pending partials: it is the iteration's first launch where the loop
+// kernel transforms its divergence itself. Blocks that see the stop flag it may raise leave Z as it is and
+// others may not, so Z is stale once the loop has stopped.
 template <typename T, int NZ, int NTT, int BX>
 __global__ void __launch_bounds__(ct_threads(BX * NZ * NTT, 8))
     k_fft_zt_ct(cx<T>* __restrict__ Z, size_t zps, int nx, int ny, const cx<T>* __restrict__ twgz,
                 const cx<T>* __restrict__ twgt, const T* __restrict__ sin2, T coef, int no_fa,
-                const Ctl* __restrict__ ctl, int force, const T* __restrict__ mtab, TupleGeom tg,
-                cx<T>* __restrict__ spec, Batch bt) {
+                Ctl* ctl, int force, const T* __restrict__ mtab, TupleGeom tg, cx<T>* __restrict__ spec,
+                const double2* __restrict__ part, int npart, double inv3v, double inv12v, Batch bt) {
     // LDS row pitch NZ*BX + BX: along a z row the lanes step through (x, t) as xo + TSP*t, so with
     // TSP = BX (mod the number of element slots per LDS cycle) consecutive lanes land in consecutive
     // slots; a pitch of NZ*BX + 1 put the lanes of neighbouring t rows on the same slots when BX > 1
@@ -134,6 +137,12 @@ __global__ void __launch_bounds__(ct_threads(BX * NZ * NTT, 8))
         twgt = bshift(twgt, bo);
         sin2 = bshift(sin2, bo);
         ctl = bshift(ctl, bo);
+        part = bshift(part, bo);
+    }
+    const int red = part != nullptr ? 1 : 0;
+    if (red && blockIdx.x == 0) {
+        if (ctl->pending) reduce_partials(part, npart, inv3v, inv12v, ctl, 1);
+        return;
     }
     if (!force && ctl->done) return;
     __shared__ cx<T> twz[NZ], twt[NTT], buf[NTT * TSP];
@@ -144,7 +153,7 @@ __global__ void __launch_bounds__(ct_threads(BX * NZ * NTT, 8))
     for (int i = threadIdx.x; i < ny; i += NT) s2[kZtMaxXY + i] = sin2[nx + i];
     for (int i = threadIdx.x; i < NZ + NTT; i += NT) s2[2 * kZtMaxXY + i] = sin2[nx + ny + i];
     const int nxb = nx / BX;
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int blk = xcd_remap(blockIdx.x - red, gridDim.x - red);
     const int xb = blk % nxb;
     const int rest = blk / nxb;
     const int y = rest % ny, f = rest / ny;

@@ -72,8 +72,8 @@ template <typename T, int NZ, int NTT, int BX>
 __global__ void __launch_bounds__(BX*(NZ > NTT ? NZ : NTT))
     k_fft_zt_reg(cx<T>* __restrict__ Z, size_t zps, int nx, int ny, const cx<T>* __restrict__ twgz,
                  const cx<T>* __restrict__ twgt, const T* __restrict__ sin2, T coef, int no_fa,
-                 const Ctl* __restrict__ ctl, int force, const T* __restrict__ mtab, TupleGeom tg,
-                 cx<T>* __restrict__ spec, Batch bt) {
+                 Ctl* ctl, int force, const T* __restrict__ mtab, TupleGeom tg, cx<T>* __restrict__ spec,
+                 const double2* __restrict__ part, int npart, double inv3v, double inv12v, Batch bt) {
     constexpr int TP = NZ * BX + BX;
     {
         const size_t bo = boff(bt);
@@ -82,11 +82,17 @@ __global__ void __launch_bounds__(BX*(NZ > NTT ? NZ : NTT))
         twgt = bshift(twgt, bo);
         sin2 = bshift(sin2, bo);
         ctl = bshift(ctl, bo);
+        part = bshift(part, bo);
+    }
+    const int red = part != nullptr ? 1 : 0;  // with part set, block 0 reduces the loop kernel's partials
+    if (red && blockIdx.x == 0) {
+        if (ctl->pending) reduce_partials(part, npart, inv3v, inv12v, ctl, 1);
+        return;
     }
     if (!force && ctl->done) return;
     __shared__ cx<T> buf[NTT * TP];
     const int nxb = nx / BX;
-    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int blk = xcd_remap(blockIdx.x - red, gridDim.x - red);
     const int xb = blk % nxb;
     const int rest = blk / nxb;
     const int y = rest % ny, f = rest / ny;

@@ -17,7 +17,10 @@
 //   k_update_measure  the links H U0 H(x+mu)^dag of H_{k+1}: their divergence
 //                   -> D, FP64 block partials of F and theta
 // The partials are reduced by the next iteration's k_fft_xy (or by k_finalize
-// before the host reads the control block), in a fixed order.
+// before the host reads the control block), in a fixed order. On square planes of
+// 8, 12, 16 and 32 with enough of them, k_measure_xy takes the place of
+// k_update_measure and of the next k_fft_xy (three launches per iteration) and
+// k_fft_zt's first block reduces.
 //
 // Delta is traceless anti-Hermitian, so it is carried as four complex fields:
 // Z0 = Delta01, Z1 = Delta02, Z2 = Delta12, Z3 = d0 + i d1 with Delta00 = i d0,

@@ -1,0 +1,102 @@
+"""The loop kernel that measures and transforms in (x, y) at once: shapes at the edges of its rule, plane
+orders, and its transform buffer across the calls that use the same memory.
+
+Against the FP64 oracle: in double the bounds of the loop test of every shape (links 1e-12, theta 1e-10
+relative, F 1e-13). In float a link is a product of three matrices (2 x 3 terms of up to 6 x 6e-8 each) formed
+from rows that each update rounds again, so 1e-6 an update and 5e-6 after three; theta and F average such errors.
+"""
+import numpy as np
+import pytest
+
+from oracle import landau
+from paper_1208_1186_amd import gf, synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gf.load()
+
+
+@pytest.mark.parametrize("dims,precision", [
+    ((8, 8, 24, 8), "fp64_18"), ((8, 8, 12, 12), "fp32_18"),
+    ((12, 12, 8, 8), "fp32_12"), ((12, 12, 8, 8), "fp64_12"),      # part waves; in double the two launches
+    ((16, 16, 32, 4), "fp64_18"), ((16, 16, 12, 12), "fp64_12"),   # first plane counts of its rule; bricks of 4 x 4
+    ((16, 16, 8, 8), "fp32_12"), ((32, 32, 32, 4), "fp64_12"),     # below it: the two launches
+    ((32, 32, 16, 16), "fp64_12"), ((32, 32, 48, 8), "fp32_12"),
+])
+def test_updates_match_oracle(dims, precision):
+    print(f"joined loop {dims} {precision}", flush=True)
+    n = 3 if np.prod(dims) < 1 << 17 else 1
+    u = synth.make_config(dims, 31)
+    links = torch.from_numpy(u).cuda()
+    fx = gf.GaugeFixer(links, precision, check_every=2)
+    fx.iterate(n)
+    ref, hist = u, [(landau.theta(u), landau.functional(u))]
+    for _ in range(n):
+        ref, *_ = landau.fa_step(ref, 0.08)
+        hist.append((landau.theta(ref), landau.functional(ref)))
+    th, f = fx.history(n + 1)
+    fx.close()
+    want = np.array(hist)
+    dl, dth, df = (5e-6, 1e-4, 1e-5) if precision.startswith("fp32") else (1e-12, 1e-10, 1e-13)
+    assert np.max(np.abs(links.cpu().numpy() - ref)) < dl
+    assert np.max(np.abs(th - want[:, 0]) / want[:, 0]) < dth
+    assert np.max(np.abs(f - want[:, 1])) < df
+
+
+@pytest.mark.parametrize("dims,precision", [((16, 16, 24, 8), "fp64_18"), ((8, 8, 12, 12), "fp64_12"),
+                                            ((12, 12, 16, 16), "fp32_12")])
+def test_plane_orders_are_bitwise_equal(dims, precision):
+    u = synth.make_config(dims, 32)
+    runs = []
+    for zb in (1, 2, 4, 8, 0, -1):
+        links = torch.from_numpy(u).cuda()
+        fx = gf.GaugeFixer(links, precision)
+        try:
+            fx.set_loop_traversal(zb)
+        except gf.GfError:
+            continue
+        fx.iterate(7)
+        runs.append((links, fx.history(8)))
+        fx.close()
+    assert len(runs) >= 2
+    for links, h in runs[1:]:
+        assert torch.equal(links, runs[0][0])
+        assert np.array_equal(h[0], runs[0][1][0]) and np.array_equal(h[1], runs[0][1][1])
+
+
+@pytest.mark.parametrize("precision", ["fp64_18", "fp32_12"])
+def test_other_uses_of_the_transform_buffer(precision):
+    """Stage calls, a saved and restored state and a stop between updates leave the iterates what they are in
+    one uninterrupted run."""
+    dims = (8, 8, 24, 8)
+    u = synth.make_config(dims, 33)
+    la = torch.from_numpy(u).cuda()
+    a = gf.GaugeFixer(la, precision, check_every=4)
+    tol = a.iterate(9).theta * 1.000001  # a stop after 9 updates, one into the third check interval
+    l9 = la.clone()
+    a.iterate(8)
+    lb = torch.from_numpy(u).cuda()
+    b = gf.GaugeFixer(lb, precision, check_every=4)
+    field = torch.randn(u.shape[:4] + (3, 3), dtype=torch.complex128, device="cuda")
+    out = torch.empty_like(field)
+    b.iterate(2)
+    gf.gf_stage_divergence(b.ctx, out.data_ptr())
+    b.iterate(1)
+    gf.gf_stage_filter(b.ctx, field.data_ptr(), out.data_ptr())
+    b.iterate(1)
+    gf.gf_stage_gauge(b.ctx, field.data_ptr(), out.data_ptr())
+    state = b.save_state()
+    b.iterate(3)
+    b.load_state(state)
+    r = b.fix_until(tol, 100)
+    assert r.iters == 9 and torch.equal(lb, l9)
+    b.iterate(8)
+    assert torch.equal(lb, la)
+    a.close()
+    b.close()
