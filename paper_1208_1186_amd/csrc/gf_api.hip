@@ -457,11 +457,11 @@ const cx<T>* twp(gf_ctx* c, int d) {
 #define GF_ZT_CASES_F64(X)                                                                                     \
     X(8, 8, 4) X(8, 8, 8) X(12, 12, 2) X(12, 12, 4) X(16, 16, 4) X(16, 16, 8) X(16, 16, 16) X(24, 8, 4)        \
     X(24, 8, 8) X(32, 4, 4) X(32, 4, 8) X(32, 4, 16) X(48, 8, 2) X(48, 8, 4) X(48, 8, 8) X(48, 8, 16)         \
-    X(32, 32, 2) X(32, 32, 4) X(32, 64, 2)
+    X(32, 32, 2) X(32, 32, 4) X(32, 64, 2) X(32, 64, 4)
 #define GF_ZT_CASES_F32(X)                                                                                     \
     X(8, 8, 4) X(8, 8, 8) X(12, 12, 4) X(16, 16, 4) X(16, 16, 8) X(16, 16, 16) X(24, 8, 4) X(24, 8, 8)        \
     X(32, 4, 8) X(32, 4, 16) X(32, 4, 32) X(48, 8, 4) X(48, 8, 8) X(48, 8, 16) X(32, 32, 4) X(32, 32, 8)      \
-    X(32, 64, 2) X(32, 64, 4)
+    X(32, 64, 2) X(32, 64, 4) X(32, 64, 8)
 #define GF_GAUGE_CASES(X) X(8, 8) X(12, 12) X(16, 16) X(24, 24) X(32, 32) X(48, 48)
 
 bool generic_fft(const gf_ctx* c) { return (c->p.flags & (GF_FLAG_GENERIC_FFT | GF_FLAG_BATCH_FUSED)) != 0; }
@@ -1033,6 +1033,7 @@ std::vector<int> zt_candidates(const Layout& L) {
 }
 
 constexpr int kTuneReps = 10;
+constexpr size_t kL2Bytes = (size_t)8 * 4 << 20;  // eight XCDs' L2s
 constexpr int kTuneRounds = 3;
 
 // Keeps the stream busy while the host queues the trial launches behind it, so that short kernels are timed
@@ -1068,13 +1069,23 @@ double time_launches(gf_ctx* c, F run) {
     return out;
 }
 
-template <typename T>
-double time_pass(gf_ctx* c, bool xy) {
-    return time_launches(c, [&]() {
-        if (xy)
+// Where Q is larger than the L2s, a (z, t) pass is timed behind the pass that writes Q in the loop. Alone, on its
+// own result of the trial before, two columns per block came out fastest on 32 x 64 planes in double and were
+// kept; in the loop they take 100 us against 88 for four (32^3 x 64), whose rows are twice as long.
+template <typename T, int NE>
+void time_pass_t(gf_ctx* c, bool xy, double& ms_out) {
+    const Layout& L = c->L;
+    const bool behind = 4 * (size_t)L.vol * sizeof(cx<T>) > kL2Bytes;
+    ms_out = time_launches(c, [&]() {
+        if (xy) {
             launch_xy<T, false>(c, c->D, c->Q, 1, false);
-        else
-            launch_zt<T>(c, c->Q, 1);
+            return;
+        }
+        if (behind && L.strips)
+            launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, 1);
+        else if (behind)
+            launch_xy<T, false>(c, c->D, c->Q, 1, false);
+        launch_zt<T>(c, c->Q, 1);
     });
 }
 
@@ -1131,12 +1142,15 @@ gf_status autotune(gf_ctx* c) {
                     set_xy_tile(c->L, cand[i]);
                 else
                     set_zt_tile(c->L, cand[i]);
-                t[i] = std::min(t[i], c->L.fp32 ? time_pass<float>(c, xy) : time_pass<double>(c, xy));
+                double ms = 1e30;
+                GF_DISPATCH(c, time_pass_t, c, xy, ms);
+                t[i] = std::min(t[i], ms);
             }
         bestv = cand[std::min_element(t.begin(), t.end()) - t.begin()];
     };
     if (xs.size() > 1 && c->L.strips == 0) pick(xs, true, bestG);  // (no forward (x, y) pass in a joined loop)
     set_xy_tile(c->L, bestG);
+    (void)hipMemsetAsync(c->tune_ctl, 0, offsetof(Ctl, hist_theta), c->st);  // (trials of the joined loop kernel)
     if (zs.size() > 1) pick(zs, false, bestB);
     set_zt_tile(c->L, bestB);
     int bestZ = 1;
