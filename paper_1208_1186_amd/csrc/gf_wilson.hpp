@@ -209,6 +209,98 @@ __global__ void __launch_bounds__(1024) k_wcorr_xy_inv(const cx<double>* __restr
     }
 }
 
+// The same three passes for the extents compiled in (GF_W_PLANES, GF_W_LINES): transforms as templates, a
+// butterfly or two per thread and stage. At 48^3 x 8 the passes move 16 MB each way between memory-side cache and
+// a few hundred blocks (432, 576 and 48), so each is one round of blocks and takes as long as its chain of
+// loads, stages and barriers: more threads per block shorten it, and the first stage reads memory itself. The y
+// transforms come first there, since their rows are runs of Nx sites. Measured at 48^3 x 8 (us): forward (x, y)
+// 15.1 -> 11.1, z 16.8 -> 8.8, inverse 9.9 -> 5.5.
+constexpr int wcorr_threads(int elems, int ept) {
+    const int t = ((elems + ept - 1) / ept + 63) / 64 * 64;
+    return t > 1024 ? 1024 : t;
+}
+constexpr int kWCtEpt = 4;
+
+// Row b of the y transforms of one plane is column b, element e its y.
+template <int NX>
+struct WPlaneIn {
+    const cx<double>* g;
+    static constexpr bool lds_in = false, lds_out = false;
+    __device__ __forceinline__ cx<double> ld(int b, int e) const { return g[e * NX + b]; }
+};
+
+// One plane from memory through both transforms into LDS (rows padded to NX + 1). The first stage uses no
+// twiddles and ends in the barrier that shows them.
+template <int NX, int NY, int NT, bool INV>
+__device__ __forceinline__ void wcorr_plane_ct(cx<double>* buf, cx<double>* twx, cx<double>* twy,
+                                               const cx<double>* g, const cx<double>* twgx,
+                                               const cx<double>* twgy) {
+    for (int i = threadIdx.x; i < NX; i += NT) twx[i] = twgx[i];
+    for (int i = threadIdx.x; i < NY; i += NT) twy[i] = twgy[i];
+    using RY = Rows<NX, NX + 1, NX, 1, 0>;
+    fft_rows_io<NY, 0, 1, RY, NT, double, INV>(buf, twy, WPlaneIn<NX>{g}, LdsIo<RY, double>{buf}, threadIdx.x);
+    fft_rows_ct<NX, 0, 1, Rows<NY, 1, NY, NX + 1, 0>, NT, double, INV>(buf, twx);
+}
+
+template <int NX, int NY>
+__global__ void __launch_bounds__(wcorr_threads(NX* NY, kWCtEpt))
+    k_wcorr_xy_fwd_ct(cx<double>* __restrict__ W, size_t wps, const cx<double>* __restrict__ twgx,
+                      const cx<double>* __restrict__ twgy) {
+    constexpr int NT = wcorr_threads(NX * NY, kWCtEpt), P = NX * NY;
+    __shared__ cx<double> twx[NX], twy[NY], buf[NY * (NX + 1)];
+    cx<double>* g = W + (size_t)blockIdx.y * wps + (size_t)blockIdx.x * P;
+    wcorr_plane_ct<NX, NY, NT, false>(buf, twx, twy, g, twgx, twgy);
+    for (int e = threadIdx.x; e < P; e += NT) g[e] = buf[e / NX * (NX + 1) + e % NX];
+}
+
+template <int NX, int NY>
+__global__ void __launch_bounds__(wcorr_threads(NX* NY, kWCtEpt))
+    k_wcorr_xy_inv_ct(const cx<double>* __restrict__ Sg, const cx<double>* __restrict__ twgx,
+                      const cx<double>* __restrict__ twgy, double scale, double* __restrict__ corr) {
+    constexpr int NT = wcorr_threads(NX * NY, kWCtEpt), P = NX * NY;
+    __shared__ cx<double> twx[NX], twy[NY], buf[NY * (NX + 1)];
+    wcorr_plane_ct<NX, NY, NT, true>(buf, twx, twy, Sg + (size_t)blockIdx.x * P, twgx, twgy);
+    double* out = corr + (size_t)blockIdx.x * P;
+    for (int e = threadIdx.x; e < P; e += NT) out[e] = buf[e / NX * (NX + 1) + e % NX].re * scale;
+}
+
+// Row b of the z transforms is column b % BX of element b / BX (the sum's rows: of S), entry e its z.
+template <int BX>
+struct WColumns {
+    cx<double>* g;  // the block's first column
+    size_t wps;
+    int plane;
+    static constexpr bool lds_in = false, lds_out = false;
+    __device__ __forceinline__ size_t at(int b, int e) const {
+        return (size_t)(b / BX) * wps + (size_t)e * plane + b % BX;
+    }
+    __device__ __forceinline__ cx<double> ld(int b, int e) const { return g[at(b, e)]; }
+    __device__ __forceinline__ void st(int b, int e, cx<double> v) const { g[at(b, e)] = v; }
+};
+
+template <int NZ, int BX>
+__global__ void __launch_bounds__(wcorr_threads(9 * NZ * BX, kWCtEpt))
+    k_wcorr_z_ct(cx<double>* __restrict__ W, size_t wps, int plane, const cx<double>* __restrict__ twgz,
+                 cx<double>* __restrict__ Sg) {
+    constexpr int NT = wcorr_threads(9 * NZ * BX, kWCtEpt), E = BX * NZ;
+    __shared__ cx<double> twz[NZ], buf[9 * E], sb[E];
+    const int q0 = xcd_remap(blockIdx.x, gridDim.x) * BX;  // neighbours share 128-byte lines: on one XCD
+    for (int i = threadIdx.x; i < NZ; i += NT) twz[i] = twgz[i];
+    using RF = Rows<9 * BX, BX, BX, 1, E>;
+    using RS = Rows<BX, BX, BX, 1, 0>;
+    fft_rows_io<NZ, 0, 1, RF, NT, double, false>(buf, twz, WColumns<BX>{W + q0, wps, plane}, LdsIo<RF, double>{buf},
+                                                 threadIdx.x);
+    for (int e = threadIdx.x; e < E; e += NT) {
+        double s = 0.0;
+#pragma unroll
+        for (int f = 0; f < 9; ++f) s += norm2(buf[f * E + e]);
+        sb[e] = {s, 0.0};
+    }
+    __syncthreads();
+    fft_rows_io<NZ, 0, 1, RS, NT, double, true>(sb, twz, LdsIo<RS, double>{sb}, WColumns<BX>{Sg + q0, 0, plane},
+                                                threadIdx.x);
+}
+
 // Shell means: wave s sums corr over members[off[s] .. off[s+1]) lane-strided, then a fixed butterfly.
 __global__ void __launch_bounds__(256) k_wcorr_shells(const double* __restrict__ corr, const int* __restrict__ off,
                                                       const int* __restrict__ members, int nshell,

@@ -44,6 +44,7 @@ struct gf_wilson {
 namespace {
 
 constexpr int kWEpt = 4;  // FFT elements per thread per stage (small blocks of short work: more waves)
+constexpr int kWColumns = 4;  // x columns per block of the z pass: 64-byte runs; the plane (even extents) divides
 constexpr int kWMaxExtent = 64;
 constexpr size_t kWAlign = 256;
 
@@ -170,6 +171,53 @@ void raise_wilson_lds() {
     done = true;
 }
 
+// Planes and z extents with compiled passes (those of the lattices in use); all others take the run-time ones.
+#define GF_W_PLANES(X) X(8, 8) X(12, 12) X(16, 16) X(24, 24) X(32, 32) X(48, 48)
+#define GF_W_LINES(X) X(4) X(8) X(12) X(16) X(24) X(32) X(48)
+
+void launch_xy_fwd(gf_wilson* w) {
+    const int nx = w->n[0], ny = w->n[1], nz = w->n[2];
+#define GF_X(A, B)                                                                                                 \
+    if (nx == A && ny == B) {                                                                                      \
+        hipLaunchKernelGGL((k_wcorr_xy_fwd_ct<A, B>), dim3(nz, 9), dim3(wcorr_threads(A * B, kWCtEpt)), 0, w->st,   \
+                           w->W, w->wps, w->tw[0], w->tw[1]);                                                      \
+        return;                                                                                                    \
+    }
+    GF_W_PLANES(GF_X)
+#undef GF_X
+    hipLaunchKernelGGL(k_wcorr_xy_fwd<kWEpt>, dim3(nz, 9), dim3(w->thr_xy), w->lds_xy, w->st, w->W, w->wps, nx, ny,
+                       w->rs, w->px, w->py, w->tw[0], w->tw[1]);
+}
+
+void launch_z(gf_wilson* w) {
+    const int plane = w->n[0] * w->n[1], nz = w->n[2];
+#define GF_X(A)                                                                                                    \
+    if (nz == A) {                                                                                                 \
+        hipLaunchKernelGGL((k_wcorr_z_ct<A, kWColumns>), dim3(plane / kWColumns),                                  \
+                           dim3(wcorr_threads(9 * A * kWColumns, kWCtEpt)), 0, w->st, w->W, w->wps, plane, w->tw[2], \
+                           w->S);                                                                                  \
+        return;                                                                                                    \
+    }
+    GF_W_LINES(GF_X)
+#undef GF_X
+    hipLaunchKernelGGL(k_wcorr_z<kWEpt>, dim3(plane / w->bx), dim3(w->thr_z), w->lds_z, w->st, w->W, w->wps, plane,
+                       nz, w->bx, w->pz, w->tw[2], w->S);
+}
+
+void launch_xy_inv(gf_wilson* w, double scale, double* corr) {
+    const int nx = w->n[0], ny = w->n[1], nz = w->n[2];
+#define GF_X(A, B)                                                                                                 \
+    if (nx == A && ny == B) {                                                                                      \
+        hipLaunchKernelGGL((k_wcorr_xy_inv_ct<A, B>), dim3(nz), dim3(wcorr_threads(A * B, kWCtEpt)), 0, w->st, w->S, \
+                           w->tw[0], w->tw[1], scale, corr);                                                       \
+        return;                                                                                                    \
+    }
+    GF_W_PLANES(GF_X)
+#undef GF_X
+    hipLaunchKernelGGL(k_wcorr_xy_inv<kWEpt>, dim3(nz), dim3(w->thr_xy), w->lds_xy, w->st, w->S, nx, ny, w->rs, w->px,
+                       w->py, w->tw[0], w->tw[1], scale, corr);
+}
+
 template <int C, int STRIDE>
 void launch_lines(gf_wilson* w, const double* links, double* lines) {
     hipLaunchKernelGGL((k_wilson_lines<C, STRIDE>), dim3((w->vs + kWlSites - 1) / kWlSites), dim3(64 * C), 0, w->st,
@@ -253,9 +301,7 @@ gf_status gf_wilson_create(gf_wilson** out, const int32_t* dims, void* d_workspa
     w->rs = nx + 1;  // odd row stride: the y transform's columns fall in different LDS banks
     w->thr_xy = std::min(1024, std::max(64, wround64((nx * ny + kWEpt - 1) / kWEpt)));
     w->lds_xy = (size_t)(nx + ny + (size_t)w->rs * ny) * sizeof(cx<double>);
-    const int plane = nx * ny;
-    w->bx = 4;  // 64-byte runs per z row; the plane (both extents even) always divides
-    (void)plane;
+    w->bx = kWColumns;
     w->thr_z = std::min(1024, std::max(64, wround64((9 * w->bx * nz + kWEpt - 1) / kWEpt)));
     w->lds_z = (size_t)(nz + (size_t)10 * w->bx * nz) * sizeof(cx<double>);
     // host tables: twiddles, shells (ordered by r^2, members by site index)
@@ -340,7 +386,6 @@ namespace {
 
 gf_status correlator(gf_wilson* w, const double* d_links, bool temporal_only, double* d_lines, double* d_corr,
                      double* d_shell) {
-    const int nx = w->n[0], ny = w->n[1], nz = w->n[2];
     double* corr = d_corr ? d_corr : w->corr;
     if (temporal_only)
         launch_lines_c<9>(w, d_links, d_lines);
@@ -348,15 +393,12 @@ gf_status correlator(gf_wilson* w, const double* d_links, bool temporal_only, do
         launch_lines_c<36>(w, d_links, d_lines);
     gf_status s = wcheck(w, hipGetLastError(), "wilson lines launch");
     if (s != GF_OK) return s;
-    hipLaunchKernelGGL(k_wcorr_xy_fwd<kWEpt>, dim3(nz, 9), dim3(w->thr_xy), w->lds_xy, w->st, w->W, w->wps, nx, ny,
-                       w->rs, w->px, w->py, w->tw[0], w->tw[1]);
+    launch_xy_fwd(w);
     if ((s = wcheck(w, hipGetLastError(), "xy forward launch")) != GF_OK) return s;
-    hipLaunchKernelGGL(k_wcorr_z<kWEpt>, dim3(nx * ny / w->bx), dim3(w->thr_z), w->lds_z, w->st, w->W, w->wps,
-                       nx * ny, nz, w->bx, w->pz, w->tw[2], w->S);
+    launch_z(w);
     if ((s = wcheck(w, hipGetLastError(), "z pass launch")) != GF_OK) return s;
     const double vs = (double)w->vs;
-    hipLaunchKernelGGL(k_wcorr_xy_inv<kWEpt>, dim3(nz), dim3(w->thr_xy), w->lds_xy, w->st, w->S, nx, ny, w->rs,
-                       w->px, w->py, w->tw[0], w->tw[1], 1.0 / (3.0 * vs * vs), corr);
+    launch_xy_inv(w, 1.0 / (3.0 * vs * vs), corr);
     if ((s = wcheck(w, hipGetLastError(), "xy inverse launch")) != GF_OK) return s;
     if (d_shell) {
         hipLaunchKernelGGL(k_wcorr_shells, dim3((w->nshell + 3) / 4), dim3(256), 0, w->st, corr, w->off, w->members,

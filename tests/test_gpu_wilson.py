@@ -59,6 +59,25 @@ def test_matches_oracle_elementwise(dims, seed):
     assert np.max(np.abs(shell - wmean)) < TOL
 
 
+@pytest.mark.parametrize("dims", [
+    (12, 12, 4, 2), (16, 16, 6, 2), (24, 24, 8, 2),   # compiled planes; run-time z between them
+    (32, 32, 4, 2), (48, 48, 2, 2), (6, 8, 16, 2), (4, 6, 24, 2), (6, 4, 32, 2), (4, 4, 48, 2),  # compiled z
+])
+def test_compiled_passes_match_oracle(dims):
+    """Every compiled plane and z extent, with the run-time passes beside them, on random lines; bound above."""
+    print(f"wilson compiled passes {dims}", flush=True)
+    nx, ny, nz, nt = dims
+    u = np.broadcast_to(np.eye(3, dtype=np.complex128), synth.lattice_shape(dims) + (4, 3, 3)).copy()
+    u[..., 3, :, :] = synth.make_config((4, 4, 4, 4), 8)[..., 3, :, :].reshape(-1, 3, 3)[
+        np.random.default_rng(9).integers(0, 256, nt * nz * ny * nx)].reshape(nt, nz, ny, nx, 3, 3)
+    lines, corr, _, _, _ = _run(dims, u)
+    w = observables.wilson_lines(u)
+    assert np.max(np.abs(lines - w)) < TOL
+    f = np.fft.fftn(w, axes=(0, 1, 2))
+    want = np.fft.ifftn(np.sum(np.abs(f) ** 2, axis=(3, 4))).real / (3.0 * nx * ny * nz)
+    assert np.max(np.abs(corr - want)) < TOL
+
+
 def test_plane_wave_closed_form():
     """Diagonal plane-wave lines: Re C(r) = (1/3) sum_a cos(q_a . r) exactly."""
     dims = (6, 4, 8, 4)
