@@ -560,6 +560,37 @@ void raise_lds_ct() {
 #undef GF_X
 }
 
+// Elements per thread of a run-time-shaped pass with E elements in a block. A pass over few blocks takes as long as
+// one block's chain of loads, stages and barriers, which more threads shorten while the CUs have waves to spare;
+// from about three waves per SIMD on they only add barriers' waits. Measured with 2, 3, 4 and 8 ((z, t) pass in
+// double, us): 8 x 16 x 12 x 8 9.5 9.9 11.0 13.4, 12 x 18 x 8 x 24 10.5 11.1 12.2 15.2, 18^4 18.0 17.4 19.6 21.0,
+// 36 x 12 x 24 x 18 29.8 30.3 21.8 23.7, 36 x 36 x 24 x 12 46.8 41.4 39.9 36.1, 24 x 36^3 152 134 135 119; the
+// (x, y) passes and float alike. The transforms are bitwise the same.
+constexpr int kSimds = 1024;
+int pass_ept(const gf_ctx* c, int E) {
+    for (int e : {2, 3, 4})
+        if (E <= 1024 * e && 4 * c->L.vol * c->nact < (int64_t)3 * kSimds * 64 * e) return e;
+    return kEPT;
+}
+int pass_threads(int E, int ept) { return std::min(1024, std::max(64, round64((E + ept - 1) / ept))); }
+
+template <typename T, bool INV>
+auto xy_kernel(int ept) {
+    return ept == 2 ? k_fft_xy<T, 2, INV> : ept == 3 ? k_fft_xy<T, 3, INV> : ept == 4 ? k_fft_xy<T, 4, INV> : k_fft_xy<T, kEPT, INV>;
+}
+template <typename T>
+auto zt_kernel(int ept) {
+    return ept == 2 ? k_fft_zt<T, 2> : ept == 3 ? k_fft_zt<T, 3> : ept == 4 ? k_fft_zt<T, 4> : k_fft_zt<T, kEPT>;
+}
+template <typename T>
+auto gauge_kernel(int ept) {
+    return ept == 2   ? k_fft_xy_gauge<T, 2>
+           : ept == 3 ? k_fft_xy_gauge<T, 3>
+           : ept == 4 ? k_fft_xy_gauge<T, 4>
+           : ept == 8 ? k_fft_xy_gauge<T, kEPT>
+                      : k_fft_xy_gauge<T, 16>;
+}
+
 // (x, y) pass src -> dst. With loop_reduce, block 0 also reduces pending loop partials.
 template <typename T, bool INV>
 void launch_xy(gf_ctx* c, const void* src, void* dst, int force, bool loop_reduce) {
@@ -570,8 +601,9 @@ void launch_xy(gf_ctx* c, const void* src, void* dst, int force, bool loop_reduc
         tstop(c);
         return;
     }
-    hipLaunchKernelGGL((k_fft_xy<T, kEPT, INV>), dim3(4 * nzt / L.G + (loop_reduce ? 1 : 0), c->nact), dim3(L.thrA),
-                       L.ldsA, c->st,
+    const int E = L.G * L.n[0] * L.n[1], ept = pass_ept(c, E);
+    hipLaunchKernelGGL((xy_kernel<T, INV>(ept)), dim3(4 * nzt / L.G + (loop_reduce ? 1 : 0), c->nact),
+                       dim3(pass_threads(E, ept)), L.ldsA, c->st,
                        reinterpret_cast<const cx<T>*>(src), cxp<T>(dst), L.ps, L.n[0], L.n[1], nzt, L.G, L.rs,
                        c->plan[0], c->plan[1], twp<T>(c, 0), twp<T>(c, 1), c->ctl, force,
                        loop_reduce ? c->part : nullptr, L.nblk_fused, inv3v(c), inv12v(c), bt(c));
@@ -593,8 +625,9 @@ void launch_zt(gf_ctx* c, void* Z, int force, bool loop_reduce = false) {
         tstop(c);
         return;
     }
-    hipLaunchKernelGGL((k_fft_zt<T, kEPT>), dim3(4 * L.n[1] * (L.n[0] / L.bx), c->nact), dim3(L.thrB), L.ldsB,
-                       c->st, cxp<T>(Z), L.ps, L.n[0], L.n[1], L.n[2], L.n[3], L.bx, L.tsp, c->plan[2], c->plan[3],
+    const int E = L.bx * L.n[2] * L.n[3], ept = pass_ept(c, E);
+    hipLaunchKernelGGL(zt_kernel<T>(ept), dim3(4 * L.n[1] * (L.n[0] / L.bx), c->nact), dim3(pass_threads(E, ept)),
+                       L.ldsB, c->st, cxp<T>(Z), L.ps, L.n[0], L.n[1], L.n[2], L.n[3], L.bx, L.tsp, c->plan[2], c->plan[3],
                        twp<T>(c, 2), twp<T>(c, 3), reinterpret_cast<const T*>(c->sin2), (T)coef, no_fa ? 1 : 0,
                        c->ctl, force, mtab, c->tg, spec, bt(c));
     tstop(c);
@@ -610,16 +643,11 @@ void launch_gauge_pass(gf_ctx* c, int force, const void* hin, void* hout) {
         return;
     }
     const cx<T>* hi = reinterpret_cast<const cx<T>*>(hin);
-    if (L.eptC == kEPT)
-        hipLaunchKernelGGL((k_fft_xy_gauge<T, kEPT>), dim3(L.n[2] * L.n[3], c->nact), dim3(L.thrC), L.ldsC, c->st,
-                           reinterpret_cast<const cx<T>*>(c->Q), L.ps, hi, cxp<T>(hout), L.n[0], L.n[1], L.rs,
-                           c->plan[0], c->plan[1], twp<T>(c, 0), twp<T>(c, 1), c->ctl, force, bt(c),
-                           exact_exp(c));
-    else
-        hipLaunchKernelGGL((k_fft_xy_gauge<T, 16>), dim3(L.n[2] * L.n[3], c->nact), dim3(L.thrC), L.ldsC, c->st,
-                           reinterpret_cast<const cx<T>*>(c->Q), L.ps, hi, cxp<T>(hout), L.n[0], L.n[1], L.rs,
-                           c->plan[0], c->plan[1], twp<T>(c, 0), twp<T>(c, 1), c->ctl, force, bt(c),
-                           exact_exp(c));
+    const int E = 4 * L.n[0] * L.n[1], ept = L.eptC == kEPT ? pass_ept(c, E) : L.eptC;
+    hipLaunchKernelGGL(gauge_kernel<T>(ept), dim3(L.n[2] * L.n[3], c->nact),
+                       dim3(ept == L.eptC ? L.thrC : pass_threads(E, ept)), L.ldsC, c->st,
+                       reinterpret_cast<const cx<T>*>(c->Q), L.ps, hi, cxp<T>(hout), L.n[0], L.n[1], L.rs, c->plan[0],
+                       c->plan[1], twp<T>(c, 0), twp<T>(c, 1), c->ctl, force, bt(c), exact_exp(c));
     tstop(c);
 }
 
@@ -908,19 +936,19 @@ void raise_lds_limits() {
     static bool done = false;
     if (done) return;
     const int cap = (int)kLdsMax;
-    const void* fns[] = {
-        reinterpret_cast<const void*>(&k_fft_xy<double, kEPT, false>),
-        reinterpret_cast<const void*>(&k_fft_xy<double, kEPT, true>),
-        reinterpret_cast<const void*>(&k_fft_zt<double, kEPT>),
-        reinterpret_cast<const void*>(&k_fft_xy_gauge<double, kEPT>),
-        reinterpret_cast<const void*>(&k_fft_xy_gauge<double, 16>),
-        reinterpret_cast<const void*>(&k_fft_xy<float, kEPT, false>),
-        reinterpret_cast<const void*>(&k_fft_xy<float, kEPT, true>),
-        reinterpret_cast<const void*>(&k_fft_zt<float, kEPT>),
-        reinterpret_cast<const void*>(&k_fft_xy_gauge<float, kEPT>),
-        reinterpret_cast<const void*>(&k_fft_xy_gauge<float, 16>),
+    auto raise = [&](auto* f) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, cap);
     };
-    for (const void* f : fns) (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
+    for (int ept : {2, 3, 4, kEPT, 16}) {
+        raise(gauge_kernel<double>(ept));
+        raise(gauge_kernel<float>(ept));
+        raise(xy_kernel<double, false>(ept));
+        raise(xy_kernel<double, true>(ept));
+        raise(xy_kernel<float, false>(ept));
+        raise(xy_kernel<float, true>(ept));
+        raise(zt_kernel<double>(ept));
+        raise(zt_kernel<float>(ept));
+    }
     raise_lds_ct<double>();
     raise_lds_ct<float>();
     raise_lds_brick<double, 9>();
