@@ -99,6 +99,7 @@ struct Layout {
     size_t ldsA;
     // (z, t) pass
     int bx, tsp, thrB;
+    int bx_wide;  // columns of up to 128 bytes that fit (what narrow_bx starts from)
     size_t ldsB;
     // inverse (x, y) pass of four fields + gauge rows
     int thrC, eptC;
@@ -150,6 +151,17 @@ int zt_reg_bx(const Layout& L) {
     }
 #undef GF_X
     return 0;
+}
+
+// Columns per block of the run-time-shaped (z, t) pass over `copies` lattices: the widest rows, shortened down to 32
+// bytes while the CUs have fewer than two blocks each. Measured in the loop (us): 16 x 8 x 16 x 32 in double 20.0 with
+// 8 columns, 12.1 with 2, in float 26.4 with 16, 13.4 with 4; 24 x 24 x 18 x 18 38.8 with 8, 33.0 with 4; 48 x 16 x
+// 24 x 36 in float 53.3 with 8, 36.1 with 4. Short rows cost where the blocks are there anyway, so wider ones stay.
+int narrow_bx(const Layout& L, int copies) {
+    int bx = L.bx_wide;
+    const int64_t rows = (int64_t)4 * L.n[1] * copies;
+    while (bx % 2 == 0 && (size_t)bx * (L.fp32 ? 8 : 16) > 32 && rows * (L.n[0] / bx) < 512) bx /= 2;
+    return bx;
 }
 
 void plan_brick(Layout& L);
@@ -223,8 +235,11 @@ gf_status plan_plain(const gf_params* p, Layout& L, std::string& err) {
         err = "z-t plane too large for one block";
         return GF_ENOTSUP;
     }
+    const bool generic = (p->flags & (GF_FLAG_GENERIC_FFT | GF_FLAG_BATCH_FUSED)) != 0;
+    L.bx_wide = L.bx;
+    if (zt_candidates(L).empty() || (p->flags & GF_FLAG_GENERIC_FFT) != 0) L.bx = narrow_bx(L, 1);
     if (const int rb = zt_reg_bx(L)) L.bx = rb;  // the register pass of this shape
-    if ((p->flags & (GF_FLAG_GENERIC_FFT | GF_FLAG_BATCH_FUSED)) == 0) L.strips = join_strips(L);
+    if (!generic) L.strips = join_strips(L);
     set_zt_tile(L, L.bx);
     // inverse (x, y) + gauge pass: the four fields of one (z, t) plane per block.
     const int EC = 4 * nx * ny;
@@ -576,7 +591,10 @@ int pass_threads(int E, int ept) { return std::min(1024, std::max(64, round64((E
 
 template <typename T, bool INV>
 auto xy_kernel(int ept) {
-    return ept == 2 ? k_fft_xy<T, 2, INV> : ept == 3 ? k_fft_xy<T, 3, INV> : ept == 4 ? k_fft_xy<T, 4, INV> : k_fft_xy<T, kEPT, INV>;
+    return ept == 2   ? k_fft_xy<T, 2, INV>
+           : ept == 3 ? k_fft_xy<T, 3, INV>
+           : ept == 4 ? k_fft_xy<T, 4, INV>
+                      : k_fft_xy<T, kEPT, INV>;
 }
 template <typename T>
 auto zt_kernel(int ept) {
@@ -1848,7 +1866,8 @@ gf_status init_batch(gf_ctx* c, BatchState& b, double* const* d_links, unsigned 
             g.drv[ph] = d;
             carve(d, g.q[ph], g.L[ph], nullptr, ws + g.off[ph], st);
             set_xy_tile(d->L, g.view[ph][0]->L.G);  // the tiling tuned for this shape and precision
-            set_zt_tile(d->L, g.view[ph][0]->L.bx);
+            const bool compiled = !zt_candidates(d->L).empty() && (g.q[ph].flags & GF_FLAG_GENERIC_FFT) == 0;
+            set_zt_tile(d->L, compiled ? g.view[ph][0]->L.bx : b.fused ? d->L.bx_wide : narrow_bx(d->L, ng));
             d->L.zb = g.view[ph][0]->L.zb;
             d->cs = g.cs[ph];
             d->act_dev = g.d_act;
