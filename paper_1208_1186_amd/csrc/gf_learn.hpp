@@ -346,11 +346,13 @@ __device__ __forceinline__ void mlp_layer1_weights(const float* __restrict__ par
     }
 }
 
-// This lane's right operands of layer 1: features 4 s + kq of row `row` (zero past the last row).
+// This lane's right operands of layer 1: features 4 s + kq of row `row`. Past the last row those of the last one, whose
+// activations then are values of the input itself: zeros there would meet an infinite weight as NaN (with saturated
+// units the gradient of the other rows is finite), and a NaN passes the zero output gradients of these lanes.
 __device__ __forceinline__ void mlp_row_features(const float* __restrict__ X, int64_t row, int64_t n, int kq, float x[2]) {
-    const bool in = row < n;
-    x[0] = in ? X[row * kMlpIn + kq] : 0.f;
-    x[1] = !in ? 0.f : kq < 2 ? X[row * kMlpIn + 4 + kq] : kq == 2 ? 1.f : 0.f;
+    const float* r = X + (row < n ? row : n - 1) * kMlpIn;
+    x[0] = r[kq];
+    x[1] = kq < 2 ? r[4 + kq] : kq == 2 ? 1.f : 0.f;
 }
 
 __device__ __forceinline__ f32x4 tanh4(f32x4 z) { return f32x4{tanhf(z[0]), tanhf(z[1]), tanhf(z[2]), tanhf(z[3])}; }

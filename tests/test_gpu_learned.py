@@ -130,6 +130,34 @@ def test_row_groups_and_train_step(rows):
     assert torch.equal(g, g2) and torch.equal(pa, pb) and torch.equal(ma, mb) and torch.equal(va, vb)
 
 
+@pytest.mark.parametrize("rows", [1, 16, 17, 79])
+def test_saturated_units_keep_the_gradient_finite(rows):
+    """Infinite weights of layer 1 saturate their units (tanh = +-1, slope 0): outputs and gradient stay finite, also
+    where the last group of 16 rows is part empty; the bounds of the tests above."""
+    rng = np.random.default_rng(rows)
+    x = np.concatenate([rng.uniform(0.1, 0.5, (rows, 4)), rng.uniform(-1, 1, (rows, 2))], 1).astype(np.float32)
+    a = rng.uniform(0.1, 2.0, rows)
+    b = a * rng.uniform(0.5, 1.5, rows)
+    tgt = np.stack([a, b, b * b / a * 1.5], 1).astype(np.float32)
+    th = _params(11)
+    th[3 * 6 + 2], th[40 * 6] = np.inf, -np.inf  # W1[3, 2], W1[40, 0]
+    th[64 * 6 + 21] = np.inf                     # b1[21]
+    nb = gf.gf_mlp_workspace_bytes(rows, 1)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda:0")
+    g = torch.empty(gf.gf_mlp_param_count(), dtype=torch.float32, device="cuda:0")
+    o = torch.empty((rows, 2), dtype=torch.float32, device="cuda:0")
+    th_d, x_d, t_d, o_d = dev(th), dev(x), dev(tgt), dev(np.array([0, rows], np.int32))
+    gf.gf_mlp_forward(th_d.data_ptr(), x_d.data_ptr(), rows, o.data_ptr(), ws.data_ptr(), nb)
+    gf.gf_mlp_loss_grad(th_d.data_ptr(), x_d.data_ptr(), t_d.data_ptr(), o_d.data_ptr(), 1, rows, g.data_ptr(),
+                        ws.data_ptr(), nb)
+    th64 = th.astype(np.float64)
+    x64 = x.astype(np.float64)
+    want = mlp.loss_grad(th64, [(x64,) + tuple(tgt[:, k].astype(np.float64) for k in range(3))])
+    assert np.all(np.isfinite(want))
+    assert np.max(np.abs(o.cpu().numpy() - mlp.forward(th64, x64)[2])) < 1e-5
+    assert np.max(np.abs(g.cpu().numpy() - want)) <= 1e-4 * np.max(np.abs(want))
+
+
 def test_adam_step_matches_oracle():
     rng = np.random.default_rng(5)
     n = gf.gf_mlp_param_count()
