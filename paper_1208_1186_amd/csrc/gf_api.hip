@@ -2976,11 +2976,11 @@ gf_status gf_record_spectra(gf_ctx* c, int64_t n, double probe_scale, double* d_
 // ----------------------------------------------------------- training
 size_t gf_mlp_workspace_bytes(int64_t n_rows, int32_t n_samples) {
     if (n_rows < 1 || n_samples < 1) return 0;
-    const size_t nb = (size_t)mlp_bwd_blocks(n_rows);
+    const size_t np = (size_t)mlp_bwd_parts(n_rows);
     size_t o = 0;
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);       // O
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);       // dO
-    o = align_up(o + nb * kMlpParams * sizeof(float), kAlign);          // block partial gradients
+    o = align_up(o + np * kMlpParams * sizeof(float), kAlign);          // partial gradients
     o = align_up(o + (size_t)n_samples * sizeof(double), kAlign);       // sample losses
     return o;
 }
@@ -2989,19 +2989,19 @@ namespace {
 struct MlpWs {
     float *o, *dO, *gpart;
     double* sloss;
-    int nb;
+    int parts;  // partial gradients
 };
 MlpWs carve_mlp(void* ws, int64_t n_rows, int32_t n_samples) {
     MlpWs w;
     unsigned char* b = reinterpret_cast<unsigned char*>(ws);
-    w.nb = mlp_bwd_blocks(n_rows);
+    w.parts = mlp_bwd_parts(n_rows);
     size_t o = 0;
     w.o = reinterpret_cast<float*>(b + o);
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);
     w.dO = reinterpret_cast<float*>(b + o);
     o = align_up(o + (size_t)n_rows * 2 * sizeof(float), kAlign);
     w.gpart = reinterpret_cast<float*>(b + o);
-    o = align_up(o + (size_t)w.nb * kMlpParams * sizeof(float), kAlign);
+    o = align_up(o + (size_t)w.parts * kMlpParams * sizeof(float), kAlign);
     w.sloss = reinterpret_cast<double*>(b + o);
     (void)n_samples;
     return w;
@@ -3045,9 +3045,15 @@ gf_status mlp_loss_grad(const float* d_params, const float* d_x, const float* d_
     launch_mlp_forward(d_params, d_x, n_rows, w.o, st);
     hipLaunchKernelGGL(k_mlp_loss, dim3(n_samples), dim3(kLossThreads), 0, st, w.o, d_tgt, d_offsets, n_samples, w.dO,
                        w.sloss);
-    hipLaunchKernelGGL(k_mlp_backward, dim3(w.nb), dim3(256), 0, st, d_params, d_x, w.dO, n_rows, w.gpart);
+    float* gpart = w.gpart;
+    for (int64_t r = 0, per = mlp_bwd_rows(n_rows); r < n_rows; r += per) {
+        const int64_t n = std::min(per, n_rows - r);
+        hipLaunchKernelGGL(k_mlp_backward, dim3(mlp_bwd_blocks(n)), dim3(256), 0, st, d_params, d_x + r * kMlpIn,
+                           w.dO + r * kMlpOut, n, gpart);
+        gpart += (size_t)mlp_bwd_blocks(n) * kMlpParams;
+    }
     hipLaunchKernelGGL(k_grad_reduce, dim3((kMlpParams + kGradParams - 1) / kGradParams),
-                       dim3(kGradParams * kGradSlices), 0, st, w.gpart, w.nb, d_grad, step);
+                       dim3(kGradParams * kGradSlices), 0, st, w.gpart, w.parts, d_grad, step);
     gf_status s = mlp_status(hipGetLastError(), "mlp loss/gradient");
     if (s == GF_OK && h_loss) {
         std::vector<double> sl(n_samples);

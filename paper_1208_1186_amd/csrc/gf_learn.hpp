@@ -501,12 +501,29 @@ __global__ void __launch_bounds__(kLossThreads) k_mlp_loss(const float* __restri
 // the wave turns dz2, h1 and dz1 through LDS (16 x 64 each, one after another in one buffer of its own) and
 // adds to accumulators in registers; db2, dW3 and db3 are added per lane. The waves' sums are added in LDS in
 // wave order and the block's partial gradient (float) goes to gpart[b]; k_grad_reduce adds the partials in
-// block order, in double. 216 matrix instructions of 32 cycles per group: 37 us at 210k rows if the matrix
+// order, in double. 216 matrix instructions of 32 cycles per group: 37 us at 210k rows if the matrix
 // cores never waited; measured 95 (245 with dot products on the vector units and stored activations).
-constexpr int kBwdMaxBlocks = 512;  // two blocks per CU, the groups dealt out evenly
+//
+// Two blocks per CU, the groups dealt out evenly, and one launch for every kBwdRows rows (512 additions in one
+// accumulator): the rounding of the float partials stays what it is at that size, and the double sum does the rest.
+// (2^24 equal rows: the gradient is off by 7.6e-6; with all rows in one launch 1.2e-4. The training step
+// at 1.37M rows takes 623 us, 587 with one launch, 750 with as many blocks of 512 rows as that takes, 733 with the
+// partials of one launch in a loop, which spills.)
+constexpr int kBwdMaxBlocks = 512;
+constexpr int64_t kBwdRows = (int64_t)kBwdMaxBlocks * 4 * 512;
 __host__ __device__ constexpr int mlp_bwd_blocks(int64_t n) {
     const int64_t b = (n + 4 * kMlpRows - 1) / (4 * kMlpRows);
     return (int)(b < kBwdMaxBlocks ? b : kBwdMaxBlocks);
+}
+// Launches of the backward pass and rows of each (the last takes what is left).
+__host__ __device__ constexpr int mlp_bwd_launches(int64_t n) { return (int)((n + kBwdRows - 1) / kBwdRows); }
+__host__ __device__ constexpr int64_t mlp_bwd_rows(int64_t n) {
+    const int64_t l = mlp_bwd_launches(n);
+    return (n + l * kMlpRows - 1) / (l * kMlpRows) * kMlpRows;
+}
+__host__ __device__ constexpr int mlp_bwd_parts(int64_t n) {
+    const int64_t r = mlp_bwd_rows(n), l = (n + r - 1) / r;
+    return (int)(l - 1) * mlp_bwd_blocks(r) + mlp_bwd_blocks(n - (l - 1) * r);
 }
 
 __global__ void __launch_bounds__(256, 2) k_mlp_backward(const float* __restrict__ params, const float* __restrict__ X,
@@ -667,7 +684,7 @@ struct AdamStep {
     }
 };
 
-// Sum of the blocks' partial gradients in double, kGradSlices runs of consecutive blocks each in block order
+// Sum of the partial gradients in double, kGradSlices runs of consecutive partials each in order
 // and then the runs in order, and the optimiser's step if one is asked for. (One thread per parameter
 // waited on 410 dependent loads: 24 -> 6 us at 210k rows.)
 constexpr int kGradParams = 64, kGradSlices = 16;

@@ -130,6 +130,33 @@ def test_row_groups_and_train_step(rows):
     assert torch.equal(g, g2) and torch.equal(pa, pb) and torch.equal(ma, mb) and torch.equal(va, vb)
 
 
+def test_partial_gradients_stay_short():
+    """A float partial gradient is a sum of at most 512 rows in an accumulator and 4 of those, however large the batch;
+    the rest is double. With 2^24 equal rows every term of a parameter's gradient has the same size and sign, so
+    against 2^9 such rows (16 in an accumulator) the gradient may differ by (516 + 16 + 1) 2^-24 relative, the 1 for
+    the row's output gradient, which scales by a power of two."""
+    ns, th = 64, _params(12)
+    th[64 * 6 + 64 + 64 * 64 + 64 + 64:][:64] = 0.0  # W3[1]: the first rows' second output gradient stays out of the sums
+    x0 = np.array([0.3, -0.2, 0.4, 0.1, 0.6, 0.25], np.float32)
+    t0 = np.array([0.7, 0.9, 1.6], np.float32)
+    out = []
+    for n in (1 << 9, 1 << 24):
+        x_d = torch.from_numpy(x0).cuda().repeat(n, 1)
+        t_d = torch.from_numpy(t0).cuda().repeat(n, 1)
+        o_d = torch.arange(ns + 1, dtype=torch.int32, device="cuda:0") * (n // ns)
+        nb = gf.gf_mlp_workspace_bytes(n, ns)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda:0")
+        g = torch.empty(gf.gf_mlp_param_count(), dtype=torch.float32, device="cuda:0")
+        th_d = dev(th)
+        gf.gf_mlp_loss_grad(th_d.data_ptr(), x_d.data_ptr(), t_d.data_ptr(), o_d.data_ptr(), ns, n, g.data_ptr(),
+                            ws.data_ptr(), nb)
+        out.append(g.cpu().numpy().astype(np.float64))
+    assert np.all(np.isfinite(out[0])) and np.max(np.abs(out[0])) > 0.0
+    err = np.abs(out[1] - out[0])
+    print("largest relative difference", np.max(err / np.maximum(np.abs(out[0]), 1e-30)))
+    assert np.all(err <= 533 * 2.0 ** -24 * np.abs(out[0]))
+
+
 @pytest.mark.parametrize("rows", [1, 16, 17, 79])
 def test_saturated_units_keep_the_gradient_finite(rows):
     """Infinite weights of layer 1 saturate their units (tanh = +-1, slope 0): outputs and gradient stay finite, also
