@@ -130,6 +130,34 @@ def test_row_groups_and_train_step(rows):
     assert torch.equal(g, g2) and torch.equal(pa, pb) and torch.equal(ma, mb) and torch.equal(va, vb)
 
 
+def test_every_row_of_a_long_batch_matches_oracle():
+    """More groups of 16 rows than the waves of the forward pass's largest grid (4096), so that waves take a second
+    group (the one whose features were fetched meanwhile), with a part group at the end: every output by itself,
+    bound above. The backward pass's waves (2048) take up to three."""
+    rows = (33001, 40007)
+    n = sum(rows)
+    rng = np.random.default_rng(21)
+    x = np.concatenate([rng.uniform(-0.5, 0.5, (n, 4)), rng.uniform(-1, 1, (n, 2))], 1).astype(np.float32)
+    a = rng.uniform(0.1, 2.0, n)
+    b = a * rng.uniform(0.5, 1.5, n)
+    tgt = np.stack([a, b, b * b / a * rng.uniform(1.0, 2.0, n)], 1).astype(np.float32)
+    off = np.cumsum((0,) + rows).astype(np.int32)
+    th = _params(13)
+    nb = gf.gf_mlp_workspace_bytes(n, 2)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda:0")
+    out = torch.full((n, 2), float("nan"), dtype=torch.float32, device="cuda:0")
+    g = torch.empty(gf.gf_mlp_param_count(), dtype=torch.float32, device="cuda:0")
+    th_d, x_d, t_d, o_d = dev(th), dev(x), dev(tgt), dev(off)
+    gf.gf_mlp_forward(th_d.data_ptr(), x_d.data_ptr(), n, out.data_ptr(), ws.data_ptr(), nb)
+    th64, x64 = th.astype(np.float64), x.astype(np.float64)
+    assert np.max(np.abs(out.cpu().numpy() - mlp.forward(th64, x64)[2])) < 1e-5
+    gf.gf_mlp_loss_grad(th_d.data_ptr(), x_d.data_ptr(), t_d.data_ptr(), o_d.data_ptr(), 2, n, g.data_ptr(),
+                        ws.data_ptr(), nb)
+    want = mlp.loss_grad(th64, [(x64[i:j],) + tuple(tgt[i:j, k].astype(np.float64) for k in range(3))
+                                for i, j in zip(off[:-1], off[1:])])
+    assert np.max(np.abs(g.cpu().numpy() - want)) <= 1e-4 * np.max(np.abs(want))
+
+
 def test_partial_gradients_stay_short():
     """A float partial gradient is a sum of at most 512 rows in an accumulator and 4 of those, however large the batch;
     the rest is double. With 2^24 equal rows every term of a parameter's gradient has the same size and sign, so
