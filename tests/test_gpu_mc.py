@@ -87,6 +87,29 @@ def test_tiles_and_orders_match_oracle(dims, n_or, n_hits):
     m.close()
 
 
+@pytest.mark.parametrize("dims,n_hits", [
+    ((32, 16, 8, 2), 1),     # planes of 8 blocks of 64 sites: one to an XCD; z in groups
+    ((32, 16, 2, 2), 2),     # without the groups
+    ((32, 32, 4, 2), 3),     # two blocks of a plane to an XCD, without the groups
+    ((32, 32, 8, 2), 1),     # and with them
+    ((48, 32, 8, 4), 2),     # three
+    ((32, 32, 16, 10), 1),   # beyond 131072 sites one and two hits reserve LDS
+    ((32, 32, 16, 10), 2),
+])
+def test_multihit_bands_match_oracle(dims, n_hits):
+    """Planes of a multiple of eight blocks, whose bands of rows go to the XCDs: every site is written (the output is
+    NaN before) and has its own average; the bound of the tests above."""
+    print(f"multi-hit bands {dims} hits {n_hits}", flush=True)
+    u = synth.make_config((8, 8, 8, 8), 14).reshape(-1, 4, 3, 3)
+    u = u[np.random.default_rng(15).integers(0, len(u), int(np.prod(dims)))].reshape(synth.lattice_shape(dims) + (4, 3, 3))
+    m = gf.MonteCarlo(dims, 6.0, 78)
+    out = torch.full(synth.lattice_shape(dims) + (3, 3), complex("nan"), dtype=torch.complex128, device="cuda:0")
+    m.multihit(torch.from_numpy(u).cuda(), 5, n_hits, out)
+    got = out.cpu().numpy()
+    assert np.max(np.abs(got - mc.multihit(u, 6.0, 78, 5, n_hits))) < 1e-12
+    m.close()
+
+
 def test_overrelaxation_and_unitarity_at_32x32x32x32():
     dims = (32, 32, 32, 32)
     links = torch.from_numpy(synth.make_config(dims, 0)).cuda()
