@@ -228,7 +228,10 @@ gf_status gf_set_fft_tiling(gf_ctx* ctx, int32_t xy_planes, int32_t zt_columns);
  * multiple of 64 with 4*Nx*by <= 1024 and the link arrays stay below 4 GiB) on
  * the first context of a shape and precision in the process and keeps the
  * fastest. Partials are summed by site block, so every traversal
- * gives bitwise the same results. gf_set_loop_traversal overrides the choice for
+ * gives bitwise the same results. On the plane shapes whose loop kernel also
+ * transforms in (x, y) a block takes one whole (z, t) plane, partials are
+ * summed by plane, and z_group is the order of the planes (-1: bricks of 4 z by
+ * 8 t of them); the candidates and the bitwise equality are the same. gf_set_loop_traversal overrides the choice for
  * this context (a test and measurement aid); GF_EINVAL if z_group is not one
  * of the candidates. For GF_MIXED: the active phase.
  */
@@ -284,7 +287,7 @@ gf_status gf_history(gf_ctx* ctx, int64_t n, double* h_theta, double* h_F);
  * Single-stage entry points (used to check each step separately; they do not
  * advance the iteration count).
  *   gf_stage_divergence: Delta(x) of the current links -> d_delta (canonical
- *     matrix field); also refreshes theta and F.
+ *     matrix field); theta, F and the history keep their values.
  *   gf_stage_filter: d_in (canonical anti-Hermitian traceless field) ->
  *     d_out = (alpha/2) * IFFT[K(p) FFT[d_in]] (canonical matrix field).
  *   gf_stage_gauge: d_in as for gf_stage_filter -> d_out = g(x) =

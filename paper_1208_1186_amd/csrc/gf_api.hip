@@ -814,10 +814,10 @@ void raise_lds_join() {
 }
 
 // Measurement of the current links (transform in buffer k & 1): theta and F, and Delta -> D or, where the loop
-// kernel transforms (and the divergence itself is not asked for), its (x, y) transform -> Q.
+// kernel transforms, its (x, y) transform -> Q.
 template <typename T, int NE>
-void launch_measure_t(gf_ctx* c, bool want_d) {
-    const bool join = c->L.strips != 0 && !want_d;
+void launch_measure_t(gf_ctx* c) {
+    const bool join = c->L.strips != 0;
     tstart(c, GF_K_DIVERGENCE);
     if (join)
         launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->ctl, 1);
@@ -830,6 +830,16 @@ void launch_measure_t(gf_ctx* c, bool want_d) {
                        Batch{nullptr, 0});
     tstop(c);
     if (join) c->q_valid = true;
+}
+
+// Delta of the current links -> D where the loop kernel transforms. theta and F stay those of the loop's own
+// measurement (every entry point leaves them measured): this kernel sums them in another order, and they go to
+// the trial launches' control block.
+template <typename T, int NE>
+void launch_divergence_t(gf_ctx* c) {
+    tstart(c, GF_K_DIVERGENCE);
+    launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->D, 1);
+    tstop(c);
 }
 
 // Update of the current links from (alpha/2) Delta~ packed in Q: H <- reunitarize(g H) in place.
@@ -877,8 +887,15 @@ void launch_unpack_t(gf_ctx* c, double* dst) {
 
 gf_status launched(gf_ctx* c, const char* what) { return check_hip(c, hipGetLastError(), what); }
 
-gf_status launch_measure(gf_ctx* c, bool want_d = false) {
-    GF_DISPATCH(c, launch_measure_t, c, want_d);
+gf_status launch_measure(gf_ctx* c) {
+    GF_DISPATCH(c, launch_measure_t, c);
+    return launched(c, "divergence launch");
+}
+
+// Delta of the current links -> D, theta and F measured.
+gf_status launch_divergence(gf_ctx* c) {
+    if (c->L.strips == 0) return launch_measure(c);
+    GF_DISPATCH(c, launch_divergence_t, c);
     return launched(c, "divergence launch");
 }
 
@@ -2721,7 +2738,7 @@ gf_status gf_stage_divergence(gf_ctx* c, void* d_delta) {
     if (c->batch) return fail(c, GF_ESTATE, "a batch context only takes the batch calls");
     if (c->L.mixed) c = active(c);
     if (!d_delta) return fail(c, GF_EINVAL, "d_delta is NULL");
-    gf_status s = launch_measure(c, true);
+    gf_status s = launch_divergence(c);
     if (s != GF_OK) return s;
     if (c->L.fp32)
         field_unpack<float>(c, c->D, d_delta);

@@ -100,3 +100,24 @@ def test_other_uses_of_the_transform_buffer(precision):
     assert torch.equal(lb, la)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("dims,precision", [((8, 8, 24, 8), "fp64_18"), ((16, 16, 16, 16), "fp32_12"),
+                                            ((12, 12, 8, 8), "fp64_12")])
+def test_divergence_stage_leaves_the_measured_values(dims, precision):
+    """Looking at the divergence changes no reported value, not in the last bit, and is the oracle's of those links
+    (per entry: the sum of 8 links' roundings, 1e-12 in double, 1e-5 in float)."""
+    u = synth.make_config(dims, 34)
+    links = torch.from_numpy(u).cuda()
+    fx = gf.GaugeFixer(links, precision)
+    fx.iterate(2)
+    before, hist = fx.quality(), fx.history(3)
+    delta = torch.empty(u.shape[:4] + (3, 3), dtype=torch.complex128, device="cuda")
+    gf.gf_stage_divergence(fx.ctx, delta.data_ptr())
+    torch.cuda.synchronize()
+    after = fx.history(3)
+    assert fx.quality() == before
+    assert np.array_equal(after[0], hist[0]) and np.array_equal(after[1], hist[1])
+    want = landau.divergence(links.cpu().numpy())
+    assert np.max(np.abs(delta.cpu().numpy() - want)) < (1e-5 if precision.startswith("fp32") else 1e-12)
+    fx.close()
