@@ -237,7 +237,11 @@ gf_status plan_plain(const gf_params* p, Layout& L, std::string& err) {
     }
     const bool generic = (p->flags & (GF_FLAG_GENERIC_FFT | GF_FLAG_BATCH_FUSED)) != 0;
     L.bx_wide = L.bx;
-    if (zt_candidates(L).empty() || (p->flags & GF_FLAG_GENERIC_FFT) != 0) L.bx = narrow_bx(L, 1);
+    const std::vector<int> zt = zt_candidates(L);
+    if (zt.empty() || (p->flags & GF_FLAG_GENERIC_FFT) != 0)
+        L.bx = narrow_bx(L, 1);
+    else if (!generic && std::find(zt.begin(), zt.end(), L.bx) == zt.end())
+        L.bx = *std::max_element(zt.begin(), zt.end());  // of the compiled widths, where the widest is not one
     if (const int rb = zt_reg_bx(L)) L.bx = rb;  // the register pass of this shape
     if (!generic) L.strips = join_strips(L);
     set_zt_tile(L, L.bx);
@@ -747,14 +751,15 @@ void launch_loop_kernel(gf_ctx* c, const void* h, int force, Ctl* ctl, void* dst
 
 // Plane shapes whose loop kernel also takes the forward (x, y) transform (Nx, Ny, strips per plane; threads: two
 // per column and strip), and the numbers of planes from which (in double, in float) and up to which it is the
-// faster form. Per update, both launches -> joined (us), measured on each side of these lines: 8 x 8 from 64 planes
-// on 18.2 -> 15.6 (8^4), level at 144, 25 -> 22 at 384; 16 x 16 at 64 planes 22.8 -> 24.0, level at 144, 31.0 -> 27.7
-// at 192, 33.3 -> 30.7 (FP64-18), 34.6 -> 29.2 (FP64-12) and 28.3 -> 24.3 (FP32-12) at 256; 32 x 32 in double
-// at 192 60.9 -> 62.7, at 256 73.2 -> 72.5 (FP64-12 78 -> 67.7), at 384 119 -> 113, in float at 256 45.4 -> 47.9,
-// at 384 60.5 -> 58.5; 12 x 12 in float 21.1 -> 20.6 at 64 planes, 24.5 -> 23.3 at 144, 29.2 -> 27.4 at 384,
-// 37.1 -> 38.0 at 1024, in double 22.5 -> 23.6, 27.5 -> 27.2, 34.5 -> 39.0 and 52 -> 69 (five waves to a block, of
-// which two or three fit a CU). 24 x 24 and 48 x 48 planes leave LDS for a block or two per CU: 24.5 -> 26 and
-// 191 -> 217 for the two kernels.
+// faster form. Per update, both launches -> joined (us), measured on each side of these lines: 8 x 8 at 64 planes
+// 17.8-20.9 -> 15.2-16.4 (8^4), at 144 23 -> 18.5 (float 22 -> 17.5), at 384 25 -> 22; 16 x 16 level at 64 planes (22-24,
+// float 20-22), at 128 26.4 -> 25.3 (24.3 -> 21.2), at 144 29.7 -> 27.5 (25.9 -> 23.3), at 192 30.5 -> 27.3 (25.8 -> 22.5),
+// at 256 33.3 -> 30.7 (FP64-18), 33.7 -> 29.1 (FP64-12) and 26.8 -> 24.1 (FP32-12); 32 x 32 in double
+// at 144 53.0 -> 59.0, at 192 61.0 -> 63.0 (FP64-12 63.7 -> 60.8), at 256 73.5 -> 72.2 (78.2 -> 69.8), at 384 119 -> 113, in
+// float at 256 46.7 -> 48.7, at 384 60.5 -> 58.5; 12 x 12 in float 20.6 -> 19.9 at 64 planes, 23.8 -> 22.3 at 144, 24.9 -> 21.9
+// at 256, 29.2 -> 27.4 at 384, 37.1 -> 38.0 at 1024, in double level at 64 and 144 planes, 28.2 -> 27.1 at 256, 34.5 -> 39.0
+// at 384 and 52 -> 69 at 1024 (five waves to a block, of which two or three fit a CU). 24 x 24 and 48 x 48 planes leave
+// LDS for a block or two per CU: 24.5 -> 26 and 191 -> 217 for the two kernels.
 constexpr int kJoinAny = 1 << 30;
 #define GF_JOIN_CASES(X)                \
     X(8, 8, 8, 1, 1, kJoinAny)          \
@@ -762,13 +767,12 @@ constexpr int kJoinAny = 1 << 30;
     X(16, 16, 8, 128, 128, kJoinAny)    \
     X(32, 32, 4, 256, 384, kJoinAny)
 
-// Strips of this shape, or 0 for the two launches: the rule above, a compiled (z, t) tiling (those kernels can
+// Strips of this shape, or 0 for the two launches: the rule above, compiled (z, t) tilings (those kernels can
 // reduce the partials) and links under 4 GiB (32-bit offsets). The choice looks at the extents and the
 // precision only: a lattice of a batch sums its partials as it does alone.
 int join_strips(const Layout& L) {
     if ((size_t)4 * L.ne * L.ps * (L.fp32 ? 8 : 16) >= ((size_t)1 << 32)) return 0;
-    const std::vector<int> zt = zt_candidates(L);
-    if (std::find(zt.begin(), zt.end(), L.bx) == zt.end()) return 0;
+    if (zt_candidates(L).empty()) return 0;
     const int planes = L.n[2] * L.n[3];
 #define GF_X(A, B, S, LO64, LO32, HI) \
     if (L.n[0] == A && L.n[1] == B && planes >= (L.fp32 ? LO32 : LO64) && planes <= HI) return S;

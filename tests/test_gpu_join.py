@@ -121,3 +121,30 @@ def test_divergence_stage_leaves_the_measured_values(dims, precision):
     want = landau.divergence(links.cpu().numpy())
     assert np.max(np.abs(delta.cpu().numpy() - want)) < (1e-5 if precision.startswith("fp32") else 1e-12)
     fx.close()
+
+
+@pytest.mark.parametrize("dims,precision,joined", [
+    ((8, 8, 12, 12), "fp64_18", True), ((8, 8, 12, 12), "fp32_12", True),      # widest (z, t) rows not compiled
+    ((16, 16, 12, 12), "fp64_12", True), ((16, 16, 12, 12), "fp32_18", True),
+    ((16, 16, 24, 8), "fp32_12", True), ((16, 16, 32, 4), "fp64_18", True),    # and the first number of planes
+    ((16, 16, 8, 8), "fp64_18", False), ((12, 12, 12, 12), "fp64_12", False), ((32, 32, 24, 8), "fp32_12", False),
+    ((24, 24, 12, 12), "fp32_12", False),
+])
+def test_rule_of_the_joined_loop(dims, precision, joined):
+    """Which loop a shape takes is its planes' size and number alone; its (z, t) pass is a compiled one. Bounds of
+    the first test."""
+    u = synth.make_config(dims, 35)
+    links = torch.from_numpy(u).cuda()
+    fx = gf.GaugeFixer(links, precision)
+    gf.gf_set_timing(fx.ctx, 1)
+    fx.iterate(2)
+    launches = {k: n for k, (_, n) in gf.gf_kernel_times(fx.ctx).items()}
+    tiling = fx.fft_tiling()
+    fx.set_fft_tiling(*tiling)  # an error for columns that are not compiled
+    fx.close()
+    assert launches["fft_zt_filter"] == 2 and launches["update_measure"] == 2
+    assert launches["fft_xy_fwd"] == (0 if joined else 2)
+    ref = u
+    for _ in range(2):
+        ref, *_ = landau.fa_step(ref, 0.08)
+    assert np.max(np.abs(links.cpu().numpy() - ref)) < (5e-6 if precision.startswith("fp32") else 1e-12)
