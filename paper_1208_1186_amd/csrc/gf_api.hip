@@ -1290,11 +1290,9 @@ gf_status run_loop(gf_ctx* c, double tol, int64_t max_iter, gf_result* r, bool u
     if (s == GF_OK) s = read_head(c);
     if (s != GF_OK) return s;
     const long long start = c->h_head->iters;
-    if (c->L.strips && !c->q_valid && !c->h_head->done && max_iter > 0) {
-        s = launch_measure(c);
-        if (s == GF_OK) s = read_head(c);
-        if (s != GF_OK) return s;
-    }
+    // (a measurement again gives theta and F bit for bit, so nothing of it is read back)
+    if (!c->h_head->done && max_iter > 0) s = ensure_transform(c);
+    if (s != GF_OK) return s;
     while (!c->h_head->done && c->h_head->iters - start < max_iter) {
         const int64_t left = max_iter - (c->h_head->iters - start);
         int64_t k = std::min<int64_t>(left, c->p.check_every);
@@ -1565,6 +1563,7 @@ struct StateHeader {
     int64_t k_host[3];  // this context, float child, double child
     int32_t phase, net_on, rejects, fallbacks;
     int64_t net_pause;
+    int32_t q_valid[3];  // as k_host: the saved Q holds the transform the next update starts from
 };
 static_assert(sizeof(StateHeader) <= kStateHead, "state header too large");
 
@@ -1576,7 +1575,11 @@ StateHeader state_header(const gf_ctx* c) {
     h.precision = c->p.precision;
     h.flags = c->p.flags;
     h.k_host[0] = c->k_host;
-    for (int i = 0; i < 2; ++i) h.k_host[1 + i] = c->child[i] ? c->child[i]->k_host : 0;
+    h.q_valid[0] = c->q_valid ? 1 : 0;
+    for (int i = 0; i < 2; ++i) {
+        h.k_host[1 + i] = c->child[i] ? c->child[i]->k_host : 0;
+        h.q_valid[1 + i] = c->child[i] && c->child[i]->q_valid ? 1 : 0;
+    }
     h.phase = c->phase;
     h.net_on = c->net_on ? 1 : 0;
     h.rejects = c->rejects;
@@ -1587,8 +1590,12 @@ StateHeader state_header(const gf_ctx* c) {
 
 void restore_header(gf_ctx* c, const StateHeader& h) {
     c->k_host = h.k_host[0];
+    c->q_valid = h.q_valid[0] != 0;
     for (int i = 0; i < 2; ++i)
-        if (c->child[i]) c->child[i]->k_host = h.k_host[1 + i];
+        if (c->child[i]) {
+            c->child[i]->k_host = h.k_host[1 + i];
+            c->child[i]->q_valid = h.q_valid[1 + i] != 0;
+        }
     c->phase = h.phase;
     c->net_on = h.net_on != 0;
     c->rejects = h.rejects;
@@ -2706,9 +2713,6 @@ gf_status gf_set_state(gf_ctx* c, const void* d_in, size_t bytes) {
         return fail(c, GF_EINVAL, "state was not saved from a context with these parameters");
     GF_TRY_HIP(c, hipMemcpyAsync(c->ws, in + kStateHead, c->L.total, hipMemcpyDeviceToDevice, c->st));
     restore_header(c, h);
-    c->q_valid = false;  // (a state may have been saved between stage calls)
-    for (gf_ctx* k : c->child)
-        if (k) k->q_valid = false;
     gf_ctx* a = active(c);
     gf_status st = read_head(a);
     if (st == GF_OK) st = unpack_links(a, c->links_user);

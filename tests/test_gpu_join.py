@@ -148,3 +148,30 @@ def test_rule_of_the_joined_loop(dims, precision, joined):
     for _ in range(2):
         ref, *_ = landau.fa_step(ref, 0.08)
     assert np.max(np.abs(links.cpu().numpy() - ref)) < (5e-6 if precision.startswith("fp32") else 1e-12)
+
+
+@pytest.mark.parametrize("precision", ["fp64_18", "fp32_12", "mixed"])
+def test_restored_run_measures_once(precision):
+    """A state keeps the transform its next update starts from: the run that continues it measures nothing again, and
+    does where a stage call had used the buffer before the state was saved. Iterates as without the stop."""
+    dims = (8, 8, 24, 8)
+    u = synth.make_config(dims, 36)
+    la = torch.from_numpy(u).cuda()
+    a = gf.GaugeFixer(la, precision)
+    a.iterate(3)
+    saved = a.save_state()
+    field = torch.randn(u.shape[:4] + (3, 3), dtype=torch.complex128, device="cuda")
+    gf.gf_stage_filter(a.ctx, field.data_ptr(), torch.empty_like(field).data_ptr())
+    saved_after_stage = a.save_state()
+    a.iterate(4)
+    for state, measured in ((saved, 0), (saved_after_stage, 1)):
+        lb = torch.from_numpy(u).cuda()
+        b = gf.GaugeFixer(lb, precision)
+        b.load_state(state)
+        gf.gf_set_timing(b.ctx, 1)
+        b.iterate(4)
+        assert gf.gf_kernel_times(b.ctx)["divergence"][1] == measured
+        assert torch.equal(lb, la) and b.quality() == a.quality()
+        assert all(np.array_equal(x, y) for x, y in zip(b.history(8), a.history(8)))
+        b.close()
+    a.close()
