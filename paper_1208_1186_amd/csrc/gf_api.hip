@@ -1057,9 +1057,8 @@ void stage_spectral(gf_ctx* c, void* gauge) {
 // The compile-time FFT kernels come in several tilings per plane shape ((x, y):
 // planes per block; (z, t): x columns per block). On the first context of a
 // shape and precision in a process, each alternative is timed on the
-// context's own buffers (two launches to warm up, then ten) and the fastest
-// is kept for every later context of that shape and precision. The tilings
-// compute bitwise the same transform.
+// context's own buffers and the fastest is kept for every later context of
+// that shape and precision. The tilings compute bitwise the same transform.
 struct TuneKey {
     int n[4];
     bool fp32;
@@ -1099,61 +1098,81 @@ std::vector<int> zt_candidates(const Layout& L) {
     return v;
 }
 
-constexpr int kTuneReps = 10;
 constexpr size_t kL2Bytes = (size_t)8 * 4 << 20;  // eight XCDs' L2s
 constexpr int kTuneRounds = 3;
 
-// Keeps the stream busy while the host queues the trial launches behind it, so that short kernels are timed
+// Bytes of the four packed fields in Q.
+size_t field_bytes(const Layout& L) { return 4 * (size_t)L.vol * (L.fp32 ? 8 : 16); }
+
+// Trial launches of an alternative in one round: to warm up, and timed. Beyond the L2s a launch takes 20 to 400 us and
+// four of them repeat to half a percent. A program's first context (ms; with two and ten launches everywhere and a delay
+// before each trial): 32^4 in double 63.7 -> 25.5, 32^3 x 64 131.9 -> 51.7, 48^3 x 8 54.0 -> 21.6, 16^4 7.3 -> 4.3, 8^4 3.4 -> 1.7.
+struct Trials {
+    int warm, timed;
+};
+Trials trials_of(const Layout& L) { return field_bytes(L) > kL2Bytes ? Trials{1, 4} : Trials{2, 8}; }
+
+// Keeps the stream busy while the host queues a round's trial launches behind it, so that short kernels are timed
 // back to back: launched one by one they take as long as the host needs per launch (about 5 us), whichever
 // tiling they are, and the choice was noise (16^4 in double kept 16 or 8 (z, t) columns, 9.3 and 8.3 us a
-// launch, over 4 columns, 6.9). Ends by the clock, and by its count if the clock stood still.
+// launch, over 4 columns, 6.9). Ends by the clock, and by its count if the clock stood still. Above kShortBytes in Q
+// the launches outlast the host's.
 __global__ void k_tune_delay(long long ticks) {
     const long long t0 = wall_clock64();
     for (int i = 0; i < (1 << 16) && wall_clock64() - t0 < ticks; ++i) __builtin_amdgcn_s_sleep(1);
 }
-constexpr long long kTuneDelayTicks = 10000;  // of the 100 MHz counter: 100 us
+constexpr long long kTuneDelayTicks = 2000;  // of the 100 MHz counter: 20 us for each alternative in the round
+constexpr size_t kShortBytes = (size_t)8 << 20;
 
-// Milliseconds of kTuneReps trial launches queued by run(), back to back, after two to warm up.
+// The fastest of n alternatives, run(i) launching the i-th once. Each is timed in kTuneRounds rounds, the order reversed
+// every round so that no place in the order is favoured (clocks still ramping up, caches still cold), and judged by
+// its best round. A round is queued as a whole and waited for once.
 template <typename F>
-double time_launches(gf_ctx* c, F run) {
-    hipEvent_t a = nullptr, b = nullptr;
-    double out = 1e30;
-    if (hipEventCreateWithFlags(&a, hipEventDisableSystemFence) == hipSuccess &&
-        hipEventCreateWithFlags(&b, hipEventDisableSystemFence) == hipSuccess) {
-        run();
-        run();
-        hipLaunchKernelGGL(k_tune_delay, dim3(1), dim3(64), 0, c->st, kTuneDelayTicks);
-        (void)hipEventRecord(a, c->st);
-        for (int i = 0; i < kTuneReps; ++i) run();
-        (void)hipEventRecord(b, c->st);
-        float ms = 1e30f;
-        if (hipGetLastError() == hipSuccess && hipEventSynchronize(b) == hipSuccess &&
-            hipEventElapsedTime(&ms, a, b) == hipSuccess)
-            out = ms;
+size_t fastest(gf_ctx* c, size_t n, F run) {
+    const Trials tr = trials_of(c->L);
+    std::vector<hipEvent_t> ev(2 * n, nullptr);
+    std::vector<double> best(n, 1e30);
+    bool ok = true;
+    for (hipEvent_t& e : ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableSystemFence) == hipSuccess;
+    for (int r = 0; r < kTuneRounds && ok; ++r) {
+        if (field_bytes(c->L) <= kShortBytes)
+            hipLaunchKernelGGL(k_tune_delay, dim3(1), dim3(64), 0, c->st, (long long)n * kTuneDelayTicks);
+        for (size_t j = 0; j < n; ++j) {
+            const size_t i = r % 2 == 0 ? j : n - 1 - j;
+            for (int k = 0; k < tr.warm; ++k) run(i);
+            (void)hipEventRecord(ev[2 * i], c->st);
+            for (int k = 0; k < tr.timed; ++k) run(i);
+            (void)hipEventRecord(ev[2 * i + 1], c->st);
+        }
+        ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(c->st) == hipSuccess;
+        for (size_t i = 0; i < n && ok; ++i) {
+            float ms = 1e30f;
+            ok = hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]) == hipSuccess;
+            if (ok) best[i] = std::min(best[i], (double)ms);
+        }
     }
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
-    return out;
+    for (hipEvent_t e : ev)
+        if (e) (void)hipEventDestroy(e);
+    return std::min_element(best.begin(), best.end()) - best.begin();
 }
 
 // Where Q is larger than the L2s, a (z, t) pass is timed behind the pass that writes Q in the loop. Alone, on its
 // own result of the trial before, two columns per block came out fastest on 32 x 64 planes in double and were
-// kept; in the loop they take 100 us against 88 for four (32^3 x 64), whose rows are twice as long.
+// kept; in the loop they take 100 us against 88 for four (32^3 x 64), whose rows are twice as long. The loop
+// kernel's traversal is chosen before: behind its slowest one the two were level (570 us both, 464 and 455 behind the
+// fastest).
 template <typename T, int NE>
-void time_pass_t(gf_ctx* c, bool xy, double& ms_out) {
-    const Layout& L = c->L;
-    const bool behind = 4 * (size_t)L.vol * sizeof(cx<T>) > kL2Bytes;
-    ms_out = time_launches(c, [&]() {
-        if (xy) {
-            launch_xy<T, false>(c, c->D, c->Q, 1, false);
-            return;
-        }
-        if (behind && L.strips)
-            launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, 1);
-        else if (behind)
-            launch_xy<T, false>(c, c->D, c->Q, 1, false);
-        launch_zt<T>(c, c->Q, 1);
-    });
+void trial_pass_t(gf_ctx* c, bool xy) {
+    const bool behind = field_bytes(c->L) > kL2Bytes;
+    if (xy) {
+        launch_xy<T, false>(c, c->D, c->Q, 1, false);
+        return;
+    }
+    if (behind && c->L.strips)
+        launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, 1);
+    else if (behind)
+        launch_xy<T, false>(c, c->D, c->Q, 1, false);
+    launch_zt<T>(c, c->Q, 1);
 }
 
 // Traversals the loop kernel can take on this shape: z groupings (1 always), 0 (blocks step through t)
@@ -1170,15 +1189,13 @@ std::vector<int> zb_candidates(const Layout& L) {
     return v;
 }
 
+// Trial launch on the current links: divergence or transform -> Q, partials of a scratch control-block head.
 template <typename T, int NE>
-void time_loop_t(gf_ctx* c, double& ms_out) {
-    // trial launches on the current links: divergence or transform -> Q, partials of a scratch control-block head
-    ms_out = time_launches(c, [&]() {
-        if (c->L.strips)
-            launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, 1);
-        else
-            launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->Q, 1);
-    });
+void trial_loop_t(gf_ctx* c) {
+    if (c->L.strips)
+        launch_join<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, 1);
+    else
+        launch_loop_kernel<T, NE>(c, c->Hb[cur(c)], 1, c->tune_ctl, c->Q, 1);
 }
 
 gf_status autotune(gf_ctx* c) {
@@ -1198,47 +1215,30 @@ gf_status autotune(gf_ctx* c) {
     }
     int bestG = c->L.G, bestB = c->L.bx;
     const std::vector<int> xs = xy_candidates(c->L), zs = zt_candidates(c->L);
-    // Each alternative is timed in kTuneRounds rounds, the order reversed every round so that no place
-    // in the order is favoured (clocks still ramping up, caches still cold), and judged by its best round.
-    auto pick = [&](const std::vector<int>& cand, bool xy, int& bestv) {
-        std::vector<double> t(cand.size(), 1e30);
-        for (int r = 0; r < kTuneRounds; ++r)
-            for (size_t j = 0; j < cand.size(); ++j) {
-                const size_t i = r % 2 == 0 ? j : cand.size() - 1 - j;
-                if (xy)
-                    set_xy_tile(c->L, cand[i]);
-                else
-                    set_zt_tile(c->L, cand[i]);
-                double ms = 1e30;
-                GF_DISPATCH(c, time_pass_t, c, xy, ms);
-                t[i] = std::min(t[i], ms);
-            }
-        bestv = cand[std::min_element(t.begin(), t.end()) - t.begin()];
-    };
-    if (xs.size() > 1 && c->L.strips == 0) pick(xs, true, bestG);  // (no forward (x, y) pass in a joined loop)
-    set_xy_tile(c->L, bestG);
-    (void)hipMemsetAsync(c->tune_ctl, 0, offsetof(Ctl, hist_theta), c->st);  // (trials of the joined loop kernel)
-    if (zs.size() > 1) pick(zs, false, bestB);
-    set_zt_tile(c->L, bestB);
-    int bestZ = 1;
+    // trial launches write Q, the block partials and a scratch control-block head; D, the control block, the links and
+    // the transform are left as they are
+    (void)hipMemsetAsync(c->tune_ctl, 0, offsetof(Ctl, hist_theta), c->st);
     c->q_valid = false;
+    int bestZ = 1;
     const std::vector<int> zbs = zb_candidates(c->L);
-    if (zbs.size() > 1) {
-        // trial launches write Q, the block partials and a scratch control-block head; D, the control
-        // block, the links and the transform are left as they are
-        (void)hipMemsetAsync(c->tune_ctl, 0, offsetof(Ctl, hist_theta), c->st);
-        std::vector<double> tz(zbs.size(), 1e30);
-        for (int r = 0; r < kTuneRounds; ++r)
-            for (size_t j = 0; j < zbs.size(); ++j) {
-                const size_t i = r % 2 == 0 ? j : zbs.size() - 1 - j;
-                c->L.zb = zbs[i];
-                double t = 1e30;
-                GF_DISPATCH(c, time_loop_t, c, t);
-                tz[i] = std::min(tz[i], t);
-            }
-        bestZ = zbs[std::min_element(tz.begin(), tz.end()) - tz.begin()];
-    }
-    c->L.zb = bestZ;
+    if (zbs.size() > 1)
+        bestZ = zbs[fastest(c, zbs.size(), [&](size_t i) {
+            c->L.zb = zbs[i];
+            GF_DISPATCH(c, trial_loop_t, c);
+        })];
+    c->L.zb = bestZ;  // before the (z, t) trials, which may run behind the loop kernel
+    if (xs.size() > 1 && c->L.strips == 0)  // (no forward (x, y) pass in a joined loop)
+        bestG = xs[fastest(c, xs.size(), [&](size_t i) {
+            set_xy_tile(c->L, xs[i]);
+            GF_DISPATCH(c, trial_pass_t, c, true);
+        })];
+    set_xy_tile(c->L, bestG);
+    if (zs.size() > 1)
+        bestB = zs[fastest(c, zs.size(), [&](size_t i) {
+            set_zt_tile(c->L, zs[i]);
+            GF_DISPATCH(c, trial_pass_t, c, false);
+        })];
+    set_zt_tile(c->L, bestB);
     (void)hipGetLastError();
     std::lock_guard<std::mutex> lock(g_tuned_mu);
     g_tuned[key] = {bestG, bestB, bestZ};
