@@ -1058,14 +1058,17 @@ void stage_spectral(gf_ctx* c, void* gauge) {
 // planes per block; (z, t): x columns per block). On the first context of a
 // shape and precision in a process, each alternative is timed on the
 // context's own buffers and the fastest is kept for every later context of
-// that shape and precision. The tilings compute bitwise the same transform.
+// that shape and precision, two- and three-row links apart: the loop kernel's
+// traffic depends on them, and its traversal and what runs behind it with it.
+// The tilings compute bitwise the same transform.
 struct TuneKey {
     int n[4];
     bool fp32;
+    int ne;
     bool operator<(const TuneKey& o) const {
         for (int i = 0; i < 4; ++i)
             if (n[i] != o.n[i]) return n[i] < o.n[i];
-        return fp32 < o.fp32;
+        return fp32 != o.fp32 ? fp32 < o.fp32 : ne < o.ne;
     }
 };
 struct Tuned {
@@ -1203,6 +1206,7 @@ gf_status autotune(gf_ctx* c) {
     TuneKey key{};
     for (int i = 0; i < 4; ++i) key.n[i] = c->L.n[i];
     key.fp32 = c->L.fp32;
+    key.ne = c->L.ne;
     {
         std::lock_guard<std::mutex> lock(g_tuned_mu);
         auto it = g_tuned.find(key);

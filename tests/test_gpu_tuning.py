@@ -42,3 +42,24 @@ fx.advance(100)
 print(cold, 10 * (time.perf_counter() - t))
 """, repo_root))
     assert cold < 160 * update
+
+
+def test_two_and_three_row_links_are_tuned_apart(repo_root):
+    """The first context of each storage runs trials, whatever was created before it: they leave their mark in the
+    workspace (the trial launches' control block), which later contexts leave as it was."""
+    marks = _child("""
+def workspace(precision):
+    p = gf.make_params((16, 16, 16, 16), precision, 0.08, 1e-8, 10, 0)
+    u = torch.eye(3, dtype=torch.complex128, device="cuda:0").expand(16, 16, 16, 16, 4, 3, 3).contiguous()
+    n = gf.gf_workspace_bytes(p)
+    ws = torch.zeros(n + 256, dtype=torch.uint8, device="cuda:0")
+    off = -ws.data_ptr() % 256
+    ctx = gf.gf_init(p, u.data_ptr(), ws.data_ptr() + off, n, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    gf.gf_destroy(ctx)
+    return ws[off:off + n].clone()
+for first, second in (("fp64_18", "fp64_12"), ("fp32_12", "fp32_18")):
+    a, b, c, d = (workspace(p) for p in (first, second, second, second))
+    print(int(torch.equal(c, d)), int(torch.equal(b, c)))
+""", repo_root)
+    assert marks == ["1", "0", "1", "0"]
