@@ -216,7 +216,7 @@ __device__ __forceinline__ unsigned mc_plane_order(const McGeom& g, unsigned blk
 // The same for planes of a multiple of eight blocks, as dealt to the XCDs in turn: XCD k takes the k-th band of rows
 // of every plane, so that the z and t neighbours of its sites are its own on lattices of any length (one hit, against
 // consecutive planes: 32 x 64 x 8 x 8 91 -> 73 us, 32^3 x 16 288 -> 268, 32^4 548 -> 515; plain order in bands of
-// blocks without the z groups: 131 at 32^2 x 16^2 as here, 549 at 32^4).
+// blocks without the z groups: 131 at 32^2 x 16^2 as here, 549 at 32^4; all with 19 registers in scratch memory).
 __device__ __forceinline__ unsigned mc_band_order(const McGeom& g, unsigned blk, unsigned plane, unsigned threads) {
     const unsigned bpp = plane / threads;
     if (plane % threads != 0 || bpp % 8 != 0)
@@ -480,7 +480,9 @@ __global__ void __launch_bounds__(256) k_mc_count(const unsigned* __restrict__ p
 // of lines per site) and the hits by arithmetic: with two waves per SIMD one covers the other. Measured at
 // 32^4 with 8 hits: 1385 us at one wave per SIMD (260 registers), 895 at two; the staple sums in a kernel
 // of their own 1150, packing into the tiles first 1040. One-wave blocks: they spread evenly over the SIMDs
-// of a small lattice (16^4: 125 us with two-wave blocks, 88).
+// of a small lattice (16^4: 125 us with two-wave blocks, 88). The plane's products in a function of their own: as the
+// body of the loop they cost 19 registers in scratch memory instead of 4 (one hit: 32^4 514 -> 456 us,
+// 32 x 64 x 8 x 8 73 -> 64; 8 hits 895 -> 880).
 constexpr int kMhThreads = 64;
 __global__ void __launch_bounds__(kMhThreads, 2) k_mc_multihit(const double2* __restrict__ links, McGeom g, double beta,
                                                                McKey key, int nhits, double2* __restrict__ out) {
@@ -492,15 +494,15 @@ __global__ void __launch_bounds__(kMhThreads, 2) k_mc_multihit(const double2* __
         mc_coords(g, s, c);
         const McSite m = mc_neighbours(g, c);
         const unsigned s_pt = m.up[3];
-#pragma unroll 1
-        for (int nu = 0; nu < 3; ++nu) {  // not unrolled: the loads of three planes in flight take the registers
-            const unsigned s_pn = nu == 0 ? m.up[0] : nu == 1 ? m.up[1] : m.up[2];
-            const unsigned s_mn = nu == 0 ? m.dn[0] : nu == 1 ? m.dn[1] : m.dn[2];
+        auto plane = [&](int nu, unsigned s_pn, unsigned s_mn) {
             const su3<double> t = mc_mul_adj(mc_load(links, s_pt, nu), mc_load(links, s_pn, 3));
             mc_add(a, mc_mul_adj(t, mc_load(links, s, nu)));
             const su3<double> mb = mul(mc_load(links, s_mn, 3), mc_load(links, s_pt + (s_mn - s), nu));
             mc_add(a, mc_adj_mul(mb, mc_load(links, s_mn, nu)));
-        }
+        };
+#pragma unroll 1
+        for (int nu = 0; nu < 3; ++nu)  // not unrolled: the loads of three planes in flight take the registers
+            plane(nu, nu == 0 ? m.up[0] : nu == 1 ? m.up[1] : m.up[2], nu == 0 ? m.dn[0] : nu == 1 ? m.dn[1] : m.dn[2]);
     }
     su3<double> u = mc_load(links, s, 3);
     su3<double> acc = mc_zero_matrix();

@@ -220,10 +220,9 @@ gf_status gf_mc_multihit(gf_mc* m, const double* d_links, uint64_t tag, int32_t 
     if (tag > 0xFFFFFFFFull) return mfail(m, GF_EINVAL, "tag must fit in 32 bits");
     if (n_hits < 1 || n_hits > 4095) return mfail(m, GF_EINVAL, "n_hits must be in [1, 4095]");
     // One or two hits do not cover the staples, and more waves at once only turn the caches over: beyond one round of
-    // them (two a SIMD) LDS that is not used holds a CU to six or seven of the eight. Without, with seven, six and four
-    // (us): 32^4 one hit 545 527 515 525, two 550 536 540 596, three 557 557 578 680; 32^2 x 16^2 one 137 136
-    // 132 134, two 147 148 152 163; 24^2 x 16^2 one 94 87 86 93, two 105 98 103 116. Below (24^3 x 8): one 67.9 67.7
-    // 73.9 74.6.
+    // them (two a SIMD) LDS that is not used holds a CU to six or seven of the eight. Without, with seven, six and five
+    // (us): 32^4 one hit 486 467 456 453, two 490 476 481 502, three 496 502 528 570; 24^4 one 160 155 150 147, two
+    // 172 165 166 172; 32^2 x 16^2 one 121 123 120 120, two 132 136 138 143. Below (32 x 64 x 8 x 8): one 64 72 71 69.
     const bool rounds = m->g.vol > (int64_t)2 * 1024 * 64;
     const size_t lds = rounds && n_hits == 1 ? 26000 : rounds && n_hits == 2 ? 22000 : 0;
     hipLaunchKernelGGL(k_mc_multihit, dim3((unsigned)((m->g.vol + kMhThreads - 1) / kMhThreads)), dim3(kMhThreads), lds,
