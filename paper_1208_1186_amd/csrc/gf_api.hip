@@ -585,10 +585,28 @@ void raise_lds_ct() {
 // double, us): 8 x 16 x 12 x 8 9.5 9.9 11.0 13.4, 12 x 18 x 8 x 24 10.5 11.1 12.2 15.2, 18^4 18.0 17.4 19.6 21.0,
 // 36 x 12 x 24 x 18 29.8 30.3 21.8 23.7, 36 x 36 x 24 x 12 46.8 41.4 39.9 36.1, 24 x 36^3 152 134 135 119; the
 // (x, y) passes and float alike. The transforms are bitwise the same.
-constexpr int kSimds = 1024;
-int pass_ept(const gf_ctx* c, int E) {
-    for (int e : {2, 3, 4})
-        if (E <= 1024 * e && 4 * c->L.vol * c->nact < (int64_t)3 * kSimds * 64 * e) return e;
+//
+// Not where that makes a second round for a few blocks. A CU with room for `occ` waves a SIMD takes occ / ceil(w / 4)
+// blocks of w waves (they all start at the same SIMD), so nine waves of a double (z, t) pass have a CU to themselves
+// and 288 blocks run as 256 and 32. Measured (us, four elements -> the next): (z, t) pass in double 12^2 x 48 x 24
+// 36.3 -> 27.2 (eight), 12^2 x 36 x 24 29.6 (three) -> 21.5; inverse pass with the gauge step 12 x 48 x 18 x 16 25.9 -> 19.1,
+// in float 19.1 -> 15.5. Where two blocks share a CU the rounds overlap and the line is crossed for less: 576 blocks
+// of five waves, (z, t) in double 21.4 -> 22.1, gauge step in float 12.2 -> 13.6 (12 x 24^3), but in double, which keeps
+// registers in scratch memory, 20.5 -> 16.1: there the second round counts too. (Up to four waves take a SIMD each:
+// 1728 blocks of two waves, 6 x 12 x 48 x 36, 13.1 with four elements, 15.7 with eight.)
+constexpr int kSimds = 1024, kCus = 256;
+enum class Pass { xy, zt, gauge };
+int pass_ept(const gf_ctx* c, Pass pass, int E, int64_t blocks) {
+    const bool fp32 = c->L.fp32;
+    // waves a SIMD of the kernels for 2 to 4 elements, by their registers
+    const int occ = pass == Pass::gauge ? (fp32 ? 5 : 4) : pass == Pass::zt ? (fp32 ? 8 : 5) : (fp32 ? 6 : 5);
+    for (int e : {2, 3, 4}) {
+        if (E > 1024 * e || 4 * c->L.vol * c->nact >= (int64_t)3 * kSimds * 64 * e) continue;
+        const int waves = (E + 64 * e - 1) / (64 * e), per_cu = std::max(1, occ / ((waves + 3) / 4));
+        const bool counts = per_cu == 1 || (pass == Pass::gauge && !fp32 && waves > 4);
+        if (counts && blocks * c->nact > (int64_t)kCus * per_cu) continue;
+        return e;
+    }
     return kEPT;
 }
 int pass_threads(int E, int ept) { return std::min(1024, std::max(64, round64((E + ept - 1) / ept))); }
@@ -623,7 +641,7 @@ void launch_xy(gf_ctx* c, const void* src, void* dst, int force, bool loop_reduc
         tstop(c);
         return;
     }
-    const int E = L.G * L.n[0] * L.n[1], ept = pass_ept(c, E);
+    const int E = L.G * L.n[0] * L.n[1], ept = pass_ept(c, Pass::xy, E, 4 * nzt / L.G);
     hipLaunchKernelGGL((xy_kernel<T, INV>(ept)), dim3(4 * nzt / L.G + (loop_reduce ? 1 : 0), c->nact),
                        dim3(pass_threads(E, ept)), L.ldsA, c->st,
                        reinterpret_cast<const cx<T>*>(src), cxp<T>(dst), L.ps, L.n[0], L.n[1], nzt, L.G, L.rs,
@@ -647,8 +665,8 @@ void launch_zt(gf_ctx* c, void* Z, int force, bool loop_reduce = false) {
         tstop(c);
         return;
     }
-    const int E = L.bx * L.n[2] * L.n[3], ept = pass_ept(c, E);
-    hipLaunchKernelGGL(zt_kernel<T>(ept), dim3(4 * L.n[1] * (L.n[0] / L.bx), c->nact), dim3(pass_threads(E, ept)),
+    const int E = L.bx * L.n[2] * L.n[3], blocks = 4 * L.n[1] * (L.n[0] / L.bx), ept = pass_ept(c, Pass::zt, E, blocks);
+    hipLaunchKernelGGL(zt_kernel<T>(ept), dim3(blocks, c->nact), dim3(pass_threads(E, ept)),
                        L.ldsB, c->st, cxp<T>(Z), L.ps, L.n[0], L.n[1], L.n[2], L.n[3], L.bx, L.tsp, c->plan[2], c->plan[3],
                        twp<T>(c, 2), twp<T>(c, 3), reinterpret_cast<const T*>(c->sin2), (T)coef, no_fa ? 1 : 0,
                        c->ctl, force, mtab, c->tg, spec, bt(c));
@@ -665,7 +683,8 @@ void launch_gauge_pass(gf_ctx* c, int force, const void* hin, void* hout) {
         return;
     }
     const cx<T>* hi = reinterpret_cast<const cx<T>*>(hin);
-    const int E = 4 * L.n[0] * L.n[1], ept = L.eptC == kEPT ? pass_ept(c, E) : L.eptC;
+    const int E = 4 * L.n[0] * L.n[1];
+    const int ept = L.eptC == kEPT ? pass_ept(c, Pass::gauge, E, (int64_t)L.n[2] * L.n[3]) : L.eptC;
     hipLaunchKernelGGL(gauge_kernel<T>(ept), dim3(L.n[2] * L.n[3], c->nact),
                        dim3(ept == L.eptC ? L.thrC : pass_threads(E, ept)), L.ldsC, c->st,
                        reinterpret_cast<const cx<T>*>(c->Q), L.ps, hi, cxp<T>(hout), L.n[0], L.n[1], L.rs, c->plan[0],

@@ -63,3 +63,28 @@ for first, second in (("fp64_18", "fp64_12"), ("fp32_12", "fp32_18")):
     print(int(torch.equal(c, d)), int(torch.equal(b, c)))
 """, repo_root)
     assert marks == ["1", "0", "1", "0"]
+
+
+@pytest.mark.parametrize("kernel,more,fewer,work", [
+    ("fft_zt_filter", (12, 12, 48, 24), (12, 8, 48, 24), 1.5),    # 288 blocks of the run-time pass, 192
+    ("fft_xy_inv", (12, 48, 18, 16), (12, 48, 16, 16), 1.125),    # 288, 256
+])
+def test_a_few_blocks_more_than_cus_are_no_second_round(kernel, more, fewer, work):
+    """A pass with some blocks more than there are CUs takes at most a quarter longer than its work alone says, against
+    one whose blocks all have a CU (a second round takes as long as the first)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1208_1186_amd import gf
+    us = []
+    for dims in (more, fewer):
+        shape = tuple(reversed(dims)) + (4, 3, 3)
+        u = torch.eye(3, dtype=torch.complex128, device="cuda:0").expand(shape).contiguous()
+        fx = gf.GaugeFixer(u, "fp64_18", check_every=50)
+        fx.advance(50)
+        gf.gf_set_timing(fx.ctx, 1)
+        fx.advance(100)
+        ms, n = gf.gf_kernel_times(fx.ctx)[kernel]
+        us.append(1e3 * ms / n)
+        fx.close()
+    print(kernel, us, flush=True)
+    assert us[0] < 1.25 * work * us[1]
