@@ -1127,8 +1127,9 @@ constexpr int kTuneRounds = 3;
 size_t field_bytes(const Layout& L) { return 4 * (size_t)L.vol * (L.fp32 ? 8 : 16); }
 
 // Trial launches of an alternative in one round: to warm up, and timed. Beyond the L2s a launch takes 20 to 400 us and
-// four of them repeat to half a percent. A program's first context (ms; with two and ten launches everywhere and a delay
-// before each trial): 32^4 in double 63.7 -> 25.5, 32^3 x 64 131.9 -> 51.7, 48^3 x 8 54.0 -> 21.6, 16^4 7.3 -> 4.3, 8^4 3.4 -> 1.7.
+// four of them repeat to half a percent. A program's first context (ms; with two and ten launches everywhere and a
+// delay before each trial): 32^4 in double 63.7 -> 25.5, 32^3 x 64 131.9 -> 51.7, 48^3 x 8 54.0 -> 21.6, 16^4
+// 7.3 -> 4.3, 8^4 3.4 -> 1.7.
 struct Trials {
     int warm, timed;
 };
@@ -2993,14 +2994,15 @@ gf_status gf_record_spectra(gf_ctx* c, int64_t n, double probe_scale, double* d_
         c->spec_capture = nullptr;
         if (s == GF_OK && i >= 1) {
             const int a = (i - 1) & 1, b = i & 1, pb = 2 + ((i - 1) & 1);
+            const dim3 grid((c->L.ntuples + kRecordTuples - 1) / kRecordTuples);
             if (c->L.fp32)
-                hipLaunchKernelGGL(k_record_tuples<float>, dim3((c->L.ntuples + kRecordTuples - 1) / kRecordTuples), dim3(256), 0, c->st,
+                hipLaunchKernelGGL(k_record_tuples<float>, grid, dim3(256), 0, c->st,
                                    reinterpret_cast<const cx<float>*>(c->spec[a]),
                                    reinterpret_cast<const cx<float>*>(c->spec[b]),
                                    reinterpret_cast<const cx<float>*>(c->spec[pb]), c->L.ps, c->tg,
                                    d_records + (size_t)(i - 1) * recn);
             else
-                hipLaunchKernelGGL(k_record_tuples<double>, dim3((c->L.ntuples + kRecordTuples - 1) / kRecordTuples), dim3(256), 0, c->st,
+                hipLaunchKernelGGL(k_record_tuples<double>, grid, dim3(256), 0, c->st,
                                    reinterpret_cast<const cx<double>*>(c->spec[a]),
                                    reinterpret_cast<const cx<double>*>(c->spec[b]),
                                    reinterpret_cast<const cx<double>*>(c->spec[pb]), c->L.ps, c->tg,

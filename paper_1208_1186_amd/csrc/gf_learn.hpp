@@ -12,9 +12,11 @@
 //
 // Training signal, recorded on plain-FA trajectories: per tuple,
 // P_k = sum over the +-n reflections and the four packed fields of |Z(p)|^2
-// after the forward FFT, and C_k = the same sum of Re[Z_{k+1}(p) conj(Z_k(p))].
-// Loss of one sample: sum_p P (1 - m kappa)^2 / sum_p P with
-// kappa = (1 - C/P)/m0, the observed response of each mode.
+// after the forward FFT, C_k = the same sum of Re[Z_{k+1}(p) conj(Z_k(p))], and
+// E_k = the energy after a probe update with every multiplier scaled by sigma.
+// A sample pairs iterations k and k + 1: through P_k, E_k and P_{k+1} each mode
+// has a quadratic a - 2 s b + s^2 c of the factor s on its multiplier, and the
+// loss is ln(sum_p (a - 2 s b + s^2 c) / sum_p a) with s = exp(o_s(p) + o_a(0)).
 #pragma once
 
 #include "gf_device.hpp"
@@ -308,7 +310,7 @@ __global__ void __launch_bounds__(256) k_make_samples(const double* __restrict__
 }
 
 // Rows are momentum tuples of samples; sample s owns rows [off[s], off[s+1]),
-// its first row being the zero tuple. tgt row = (m0, P, kappa).
+// its first row being the zero tuple. tgt row = (a, b, c).
 
 // Both passes run on the matrix cores (v_mfma_f32_16x16x4f32: float products and sums), a wave taking 16 rows
 // at a time, everything transposed so that no operand has to change lanes between the layers: lane l holds

@@ -426,8 +426,8 @@ __global__ void __launch_bounds__(256) k_mc_pack(const double2* __restrict__ lin
     }
 }
 
-// reunit: every link is reunitarised on its way out (the end of a sweep).
-__global__ void __launch_bounds__(256) k_mc_unpack(McTiles P, McGeom g, double2* __restrict__ links, int reunit) {
+// Every link is reunitarised on its way out (the end of a call's last sweep).
+__global__ void __launch_bounds__(256) k_mc_unpack(McTiles P, McGeom g, double2* __restrict__ links) {
     __shared__ double2 row[kMcIoSites * kMcIoRow];
     const unsigned s0 = blockIdx.x * kMcIoSites;
     const unsigned left = (unsigned)g.vol - s0, ns = left < kMcIoSites ? left : kMcIoSites;
@@ -435,7 +435,7 @@ __global__ void __launch_bounds__(256) k_mc_unpack(McTiles P, McGeom g, double2*
     if (2 * i < ns) {
         const int par = (int)(q >> 5), odd = mc_site_parity(g, s0 + 2 * i) != par;
         su3<double> m = eo_load(P, (s0 >> 1) + i, par, (int)mu);
-        if (reunit) reunitarize(m);
+        reunitarize(m);
         double2* dst = row + (2 * i + odd) * kMcIoRow + mu * 9;
 #pragma unroll
         for (int k = 0; k < 9; ++k) dst[k] = {m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im};

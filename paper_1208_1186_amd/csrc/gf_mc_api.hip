@@ -191,7 +191,8 @@ gf_status gf_mc_update(gf_mc* m, double* d_links, uint64_t first_sweep, int32_t 
         for (int rep = 0; rep <= n_overrelax; ++rep)
             for (int mu = 0; mu < 4; ++mu)
                 for (int par = 0; par < 2; ++par) {
-                    hipLaunchKernelGGL(kUpdate[rep == 0 ? 0 : 1][mu], dim3(m->nblk_half), dim3(kMcThreads), rep == 0 ? kMcLdsHeatbath : kMcLdsOverrelax, m->st,
+                    const size_t lds = rep == 0 ? kMcLdsHeatbath : kMcLdsOverrelax;
+                    hipLaunchKernelGGL(kUpdate[rep == 0 ? 0 : 1][mu], dim3(m->nblk_half), dim3(kMcThreads), lds, m->st,
                                        m->P, m->g, par, m->beta, key, m->rej);
                     if ((s = mcheck(m, hipGetLastError(), "update launch")) != GF_OK) return s;
                 }
@@ -199,7 +200,7 @@ gf_status gf_mc_update(gf_mc* m, double* d_links, uint64_t first_sweep, int32_t 
         hipLaunchKernelGGL(k_mc_reunit, dim3((half + 255) / 256, 8), dim3(256), 0, m->st, m->P, half);
         if ((s = mcheck(m, hipGetLastError(), "reunitarisation launch")) != GF_OK) return s;
     }
-    hipLaunchKernelGGL(k_mc_unpack, dim3(io_blocks(m)), dim3(256), 0, m->st, m->P, m->g, links, 1);
+    hipLaunchKernelGGL(k_mc_unpack, dim3(io_blocks(m)), dim3(256), 0, m->st, m->P, m->g, links);
     if ((s = mcheck(m, hipGetLastError(), "unpack launch")) != GF_OK) return s;
     if (h_rejected) {
         hipLaunchKernelGGL(k_mc_count, dim3(1), dim3(256), 0, m->st, m->rej, m->nblk_half, m->d_count);
