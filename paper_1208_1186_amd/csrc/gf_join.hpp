@@ -11,9 +11,10 @@
 // another wave. H(x) is the y neighbour's of the previous row and the x neighbour's comes from its lane.
 // Links from below in z and t are formed from memory. There is no barrier until the plane is complete.
 //
-// Bound by the L1s' misses and by the fabric's reads: a site takes 1.34 KB through the L1s against 2.0 KB for
-// k_update_measure, which re-reads every back link's U0 and H and holds about 100 lines in flight per CU
-// whatever its occupancy (10.5-11 TB/s at every size and precision). Measured with the (x, y) pass counted
+// Bound in double by the L1s' misses and by the fabric's reads: a site takes 1.39 KB through the L1s against 2.0 KB
+// for k_update_measure, which re-reads every back link's U0 and H, and either holds 92 to 97 lines in flight per CU
+// (32^4 and 48^3 x 8, at 1.7 and 3.4 waves per SIMD; 7.7 and 10.5 TB/s). In float the vector units are nearer: 0.67 of
+// the issue slots here (32^3 x 64), 0.94 there (48^3 x 8). Measured with the (x, y) pass counted
 // (us): 32^4 FP64-18 184 against 192 + 27, FP64-12 148 against 178 + 27, 32^3 x 64 FP32-12 154 against
 // 183 + 28, 16^4 FP64-18 14.5 against 12.5 + 4, 8^4 5.5 against 4.6 + 2.8. On 48 x 48 planes (LDS for one
 // block per CU, 384 blocks at 48^3 x 8) and 24 x 24 planes it is the slower form (217 against 191, 26 against
