@@ -1587,8 +1587,10 @@ struct StateHeader {
     int64_t k_host[3];  // this context, float child, double child
     int32_t phase, net_on, rejects, fallbacks;
     int64_t net_pause;
-    int32_t q_valid[3];  // as k_host: the saved Q holds the transform the next update starts from
+    uint32_t q_valid[3];  // as k_host: kQValid where the saved Q holds the transform the next update starts from
 };
+// (a word that a shorter header does not leave there by chance: any other value means measuring again)
+constexpr uint32_t kQValid = 0x444c5651u;
 static_assert(sizeof(StateHeader) <= kStateHead, "state header too large");
 
 StateHeader state_header(const gf_ctx* c) {
@@ -1599,10 +1601,10 @@ StateHeader state_header(const gf_ctx* c) {
     h.precision = c->p.precision;
     h.flags = c->p.flags;
     h.k_host[0] = c->k_host;
-    h.q_valid[0] = c->q_valid ? 1 : 0;
+    h.q_valid[0] = c->q_valid ? kQValid : 0;
     for (int i = 0; i < 2; ++i) {
         h.k_host[1 + i] = c->child[i] ? c->child[i]->k_host : 0;
-        h.q_valid[1 + i] = c->child[i] && c->child[i]->q_valid ? 1 : 0;
+        h.q_valid[1 + i] = c->child[i] && c->child[i]->q_valid ? kQValid : 0;
     }
     h.phase = c->phase;
     h.net_on = c->net_on ? 1 : 0;
@@ -1614,11 +1616,11 @@ StateHeader state_header(const gf_ctx* c) {
 
 void restore_header(gf_ctx* c, const StateHeader& h) {
     c->k_host = h.k_host[0];
-    c->q_valid = h.q_valid[0] != 0;
+    c->q_valid = h.q_valid[0] == kQValid;
     for (int i = 0; i < 2; ++i)
         if (c->child[i]) {
             c->child[i]->k_host = h.k_host[1 + i];
-            c->child[i]->q_valid = h.q_valid[1 + i] != 0;
+            c->child[i]->q_valid = h.q_valid[1 + i] == kQValid;
         }
     c->phase = h.phase;
     c->net_on = h.net_on != 0;
